@@ -236,11 +236,10 @@ int sph_pack_boundary(const sph_particles *local, const uint32_t *boundary_idx,
  * (solids: Cauchy stress -p I + S); SPH_PASS_GRADIENT: velocity gradient L.
  * zero_first = 1 overwrites the rate entries of the targets, 0 adds to them
  * (the local-remote pass, step f, continues the sums of step e from hi + lo).
- * Summation over j runs in ascending source index (the FP64 fluid FORCE pass
- * over every target: two sums, each over every other run of four sources of
- * a row in ascending index, then added).  Both arrays must be
- * hash-sorted on `grid`.  The workspace receives a packed copy of the
- * sources' pair inputs (sized by sph_workspace_size for sources->n).
+ * The order of summation over j (four sums per target, then added) depends on
+ * the order of the particles alone, so repeated calls agree bit for bit.  Both
+ * arrays must be hash-sorted on `grid`.  The workspace (sized by
+ * sph_workspace_size for sources->n) is checked and not written.
  * Errors: SPH_ERR_ARG (precision or material mismatch, missing field,
  * sources->n at or above 2^27 = 134,217,728), SPH_ERR_WORKSPACE. */
 int sph_interact(const sph_params *params, const sph_grid *grid, int pass,
@@ -278,19 +277,17 @@ int sph_count_pairs(const sph_params *params, const sph_grid *grid, const sph_pa
  * every later call that runs a pair kernel (sph_interact,
  * sph_interact_adjoint, sph_neighbor_census) records begin_event on its
  * stream immediately before launching the pair kernel and end_event
- * immediately after, so that the kernel alone can be timed (the staging of
- * the source records and the wavefront plan run before it in the same
- * call).  NULL, NULL stops the recording.  The setting is process-wide and
+ * immediately after, so that the kernel alone can be timed.  NULL, NULL stops
+ * the recording.  The setting is process-wide and
  * meant for a benchmark that times one call at a time.
  * Errors: SPH_ERR_ARG when only one of the two handles is given. */
 int sph_set_pair_events(void *begin_event, void *end_event);
 
 /* Neighbour census of one interaction pass (Section I: a particle's
  * neighbours lie in its own bucket or the 26 around it).  Takes the arguments
- * of sph_interact without the rates and runs the same staging, wavefront
- * mapping, candidate filter, hit lists and neighbour predicate as that pass
- * would (pass and params->material choose which), but instead of the pair
- * terms it writes, for every target i, count_out[i] = the number of sources
+ * of sph_interact without the rates and runs the same wavefront mapping,
+ * candidate test, hit lists and neighbour predicate as that pass would, but
+ * instead of the pair terms it writes, for every target i, count_out[i] = the number of sources
  * j the pass evaluates (r_ij^2 < (2h)^2 on the position difference the pass
  * rebuilds; j == i and coincident particles, whose terms are exactly zero,
  * included) and checksum_out[i] = the sum modulo 2^64 of
@@ -342,8 +339,7 @@ int sph_neighbor_census(const sph_params *params, const sph_grid *grid, int pass
  *
  * The pair terms read p and c, not c0: d/dc0 comes from the EOS reverse
  * (sph_integrate_adjoint, SPH_STAGE_EOS).  The workspace (sph_workspace_size
- * for sources->n with SPH_SOLID_J2, which has room for the extra staged
- * records) receives packed copies of the sources and their cotangents.
+ * for sources->n with SPH_SOLID_J2) is checked and not written.
  * Errors: SPH_ERR_ARG (also sources->n at or above 2^27, both cotangents
  * NULL, a solid FORCE pass without S in the particles or in bar),
  * SPH_ERR_WORKSPACE, SPH_ERR_UNSUPPORTED (the Mie-Gruneisen EOS). */

@@ -133,13 +133,13 @@ bool check_particles(const sph_particles *p, const char *name, bool need_off, bo
     return true;
 }
 
-bool check_ws(void *ws, size_t bytes, uint32_t n, Workspace &w, size_t stage = 0)
+bool check_ws(void *ws, size_t bytes, uint32_t n, Workspace &w, size_t pair = 0)
 {
-    size_t need = carve(nullptr, n, stage).bytes;
+    size_t need = carve(nullptr, n, pair).bytes;
     if (!ws || bytes < need)
         return fail(SPH_ERR_WORKSPACE, "workspace of %zu bytes, need %zu for n = %u", ws ? bytes : 0, need, n),
                false;
-    w = carve(ws, n, stage);
+    w = carve(ws, n, pair);
     return true;
 }
 
@@ -171,7 +171,7 @@ const char *sph_last_error(void) { return g_err.c_str(); }
 size_t sph_workspace_size(const sph_grid *grid, uint32_t n_max, int prec, int material)
 {
     (void)grid;
-    return carve(nullptr, n_max, stage_bytes(prec, material)).bytes;
+    return carve(nullptr, n_max, pair_ws_bytes(prec, material)).bytes;
 }
 
 int sph_set_pair_events(void *begin_event, void *end_event)
@@ -290,17 +290,17 @@ int sph_interact(const sph_params *params, const sph_grid *grid, int pass, const
         return fail(SPH_ERR_ARG, "source bucket table missing or not on this grid");
     if (!check_rates(rates, pass, params->prec)) return SPH_ERR_ARG;
     if (targets->n == 0) return SPH_OK;
-    // hit records are addressed with 32-bit byte offsets (at most 32 bytes per source and array)
+    // source fields are addressed with 32-bit byte offsets, window entries with 32-bit sums
     const uint32_t src_max = 1u << 27;
     if (sources->n >= src_max) return fail(SPH_ERR_ARG, "sources.n = %u must be below %u", sources->n, src_max);
     Workspace w;
-    int staged_material = pass == SPH_PASS_FORCE ? params->material : SPH_FLUID_TAIT;
-    if (!check_ws(ws, ws_bytes, sources->n, w, stage_bytes(params->prec, staged_material))) return SPH_ERR_WORKSPACE;
+    int ws_material = pass == SPH_PASS_FORCE ? params->material : SPH_FLUID_TAIT;
+    if (!check_ws(ws, ws_bytes, sources->n, w, pair_ws_bytes(params->prec, ws_material))) return SPH_ERR_WORKSPACE;
     bool self = targets->hash == sources->hash;
     if (self && targets->n != sources->n)
         return fail(SPH_ERR_ARG, "targets and sources share their hash array but not their size");
     return hip_status(launch_interact(P, g, params->prec, pass, *targets, target_idx, n_targets_dev, *sources,
-                                      source_cells.start, self, zero_first, *rates, w, (hipStream_t)stream),
+                                      source_cells.start, zero_first, *rates, (hipStream_t)stream),
                       "sph_interact");
 }
 
@@ -328,13 +328,13 @@ int sph_neighbor_census(const sph_params *params, const sph_grid *grid, int pass
     const uint32_t src_max = 1u << 27;   // as in sph_interact
     if (sources->n >= src_max) return fail(SPH_ERR_ARG, "sources.n = %u must be below %u", sources->n, src_max);
     Workspace w;
-    int staged_material = pass == SPH_PASS_FORCE ? params->material : SPH_FLUID_TAIT;
-    if (!check_ws(ws, ws_bytes, sources->n, w, stage_bytes(params->prec, staged_material))) return SPH_ERR_WORKSPACE;
+    int ws_material = pass == SPH_PASS_FORCE ? params->material : SPH_FLUID_TAIT;
+    if (!check_ws(ws, ws_bytes, sources->n, w, pair_ws_bytes(params->prec, ws_material))) return SPH_ERR_WORKSPACE;
     bool self = targets->hash == sources->hash;
     if (self && targets->n != sources->n)
         return fail(SPH_ERR_ARG, "targets and sources share their hash array but not their size");
-    return hip_status(launch_census(P, g, params->prec, pass, *targets, target_idx, n_targets_dev, *sources,
-                                    source_cells.start, self, count_out, checksum_out, w, (hipStream_t)stream),
+    return hip_status(launch_census(P, g, params->prec, *targets, target_idx, n_targets_dev, *sources,
+                                    source_cells.start, count_out, checksum_out, (hipStream_t)stream),
                       "sph_neighbor_census");
 }
 
@@ -440,14 +440,14 @@ int sph_interact_adjoint(const sph_params *params, const sph_grid *grid, int pas
     const uint32_t src_max = 1u << 27;   // as in sph_interact
     if (sources->n >= src_max) return fail(SPH_ERR_ARG, "sources.n = %u must be below %u", sources->n, src_max);
     Workspace w;
-    if (!check_ws(ws, ws_bytes, sources->n, w, stage_bytes(params->prec, SPH_SOLID_J2))) return SPH_ERR_WORKSPACE;
+    if (!check_ws(ws, ws_bytes, sources->n, w, pair_ws_bytes(params->prec, SPH_SOLID_J2))) return SPH_ERR_WORKSPACE;
     bool self = targets->hash == sources->hash;
     if (self && targets->n != sources->n)
         return fail(SPH_ERR_ARG, "targets and sources share their hash array but not their size");
     const sph_rates none{};
     return hip_status(launch_interact_adjoint(P, g, params->prec, pass, *targets, target_idx, n_targets_dev, *sources,
-                                              source_cells.start, self, rates_bar_targets ? *rates_bar_targets : none,
-                                              rates_bar_sources ? *rates_bar_sources : none, *bar, w,
+                                              source_cells.start, rates_bar_targets ? *rates_bar_targets : none,
+                                              rates_bar_sources ? *rates_bar_sources : none, *bar,
                                               (hipStream_t)stream),
                       "sph_interact_adjoint");
 }

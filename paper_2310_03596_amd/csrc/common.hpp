@@ -195,50 +195,19 @@ inline AV<real> view(const sph_adjoint &a)
     return o;
 }
 
-// Packed pair inputs of the source particles, one record per particle so a
-// candidate costs one 16-byte load (FP32) and a pair two more:
-//   pos = (position or bucket offset x, y, z, bucket x index), va = (v, omega),
-//   vb = (rho, p, c, e), solids s0 = (S xx yy zz xy), s1 = (S xz yz, 0, 0).
-template <typename real>
-struct Vec4;
-template <>
-struct Vec4<float> {
-    using type = float4;
-};
-template <>
-struct Vec4<double> {
-    using type = double4;
-};
-
-// In the FP32 form the two records of a source that the pair body reads
-// together (va and vb; s0 and s1) sit side by side in one 32-byte pair, so a
-// hit touches two cache lines instead of three (measured: 4 % off the FORCE
-// pass on the column); the FP64 form's 32-byte records stay in separate
-// arrays (paired they were 1.5 % slower).
-template <typename real>
-constexpr uint32_t rec_stride = sizeof(real) == 4 ? 2 : 1;
-
-// Adjoint passes add two records of cotangents: r0 = (rbar 0..3) and
-// r1 = (rbar 4, 5, 0, 0) of the sources' rates (FORCE), or, for the
-// GRADIENT reverse, the velocity-gradient cotangent Lbar in vb (0..3), r0
-// (4..7) and r1.x (8).
-template <typename real>
-struct Stage {
-    using v4 = typename Vec4<real>::type;
-    v4 *pos, *va, *vb, *s0, *s1, *r0, *r1;   // all but pos: record j at [rec_stride<real> j]
-};
-
-// Bytes per source particle of the packed records: three for a fluid pass,
-// seven for material SPH_SOLID_J2 (the solid pass's two stress records and
-// the adjoint passes' two cotangent records).
-inline size_t stage_bytes(int prec, int material)
+// Bytes per source particle that a pair pass's workspace is checked for: three
+// records of four reals for a fluid pass, seven for material SPH_SOLID_J2.  The
+// pair kernel loads the sources' fields itself and touches none of it; the size
+// is part of the interface (what sph_workspace_size returns, and below which a
+// call is refused).
+inline size_t pair_ws_bytes(int prec, int material)
 {
     size_t rec = prec == SPH_FP64 ? 32 : 16;
     return rec * (material == SPH_SOLID_J2 ? 7 : 3);
 }
 
-// Workspace layout for n particles (256-byte aligned pieces).  The packed
-// source records come last; calls other than sph_interact never touch them.
+// Workspace layout for n particles (256-byte aligned pieces), the pair
+// passes' part (pair_ws_bytes) last.
 struct Workspace {
     uint32_t *keys[2];
     uint32_t *vals[2];
@@ -246,7 +215,6 @@ struct Workspace {
     uint32_t *totals;      // kMaxRadixBins
     uint32_t *counts;      // compaction block counts (+1)
     double *partials;      // kDiagPartial * reduction blocks
-    char *stage;           // n * stage bytes
     size_t bytes;
 };
 
@@ -254,7 +222,7 @@ inline uint32_t div_up(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) /
 
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
-inline Workspace carve(void *base, uint32_t n, size_t stage_per_particle)
+inline Workspace carve(void *base, uint32_t n, size_t pair_per_particle)
 {
     Workspace w;
     uint64_t nn = n > 0 ? n : 1;
@@ -275,30 +243,9 @@ inline Workspace carve(void *base, uint32_t n, size_t stage_per_particle)
     w.totals = reinterpret_cast<uint32_t *>(take(4ull * kMaxRadixBins));
     w.counts = reinterpret_cast<uint32_t *>(take(4ull * (blocks + 1)));
     w.partials = reinterpret_cast<double *>(take(8ull * kDiagPartial * blocks));
-    w.stage = take(stage_per_particle * nn);
+    take(pair_per_particle * nn);
     w.bytes = off;
     return w;
-}
-
-// Records 0 (pos), 1-2 (va, vb), 3-4 (s0, s1 for solids), then the adjoint's
-// (r0, r1): records 3-4 of a fluid adjoint, 5-6 of a solid one.
-template <typename real>
-inline Stage<real> stage_view(const Workspace &w, uint32_t n, bool solid, bool adj = false)
-{
-    using v4 = typename Vec4<real>::type;
-    Stage<real> s;
-    v4 *b = reinterpret_cast<v4 *>(w.stage);
-    size_t nn = n > 0 ? n : 1;
-    auto pair_at = [&](size_t rec, v4 *&first, v4 *&second) {
-        first = b + rec * nn;
-        second = rec_stride<real> == 2 ? first + 1 : b + (rec + 1) * nn;
-    };
-    s.pos = b;
-    pair_at(1, s.va, s.vb);
-    s.s0 = s.s1 = s.r0 = s.r1 = nullptr;
-    if (solid) pair_at(3, s.s0, s.s1);
-    if (adj) pair_at(solid ? 5 : 3, s.r0, s.r1);
-    return s;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -320,11 +267,10 @@ hipError_t launch_pack(int prec, const sph_particles &local, const uint32_t *bid
                        const sph_particles &payload, hipStream_t s);
 hipError_t launch_interact(const Params &P, const Grid &g, int prec, int pass, const sph_particles &tg,
                            const uint32_t *tidx, const uint32_t *nt, const sph_particles &sr,
-                           const uint32_t *sstart, bool self, int zero_first, const sph_rates &r,
-                           const Workspace &ws, hipStream_t s);
-hipError_t launch_census(const Params &P, const Grid &g, int prec, int pass, const sph_particles &tg,
-                         const uint32_t *tidx, const uint32_t *nt, const sph_particles &sr, const uint32_t *sstart,
-                         bool self, uint32_t *count, uint64_t *sum, const Workspace &ws, hipStream_t s);
+                           const uint32_t *sstart, int zero_first, const sph_rates &r, hipStream_t s);
+hipError_t launch_census(const Params &P, const Grid &g, int prec, const sph_particles &tg, const uint32_t *tidx,
+                         const uint32_t *nt, const sph_particles &sr, const uint32_t *sstart, uint32_t *count,
+                         uint64_t *sum, hipStream_t s);
 hipError_t launch_count_pairs(const Params &P, const Grid &g, int prec, const sph_particles &tg,
                               const uint32_t *tidx, const uint32_t *nt, const sph_particles &sr,
                               const uint32_t *sstart, bool self, uint64_t *counts, hipStream_t s);
@@ -333,9 +279,8 @@ hipError_t launch_integrate(const Params &P, int prec, int stage, const sph_part
                             hipStream_t s);
 hipError_t launch_interact_adjoint(const Params &P, const Grid &g, int prec, int pass, const sph_particles &tg,
                                    const uint32_t *tidx, const uint32_t *nt, const sph_particles &sr,
-                                   const uint32_t *sstart, bool self, const sph_rates &rbar_t,
-                                   const sph_rates &rbar_s, const sph_adjoint &bar, const Workspace &ws,
-                                   hipStream_t s);
+                                   const uint32_t *sstart, const sph_rates &rbar_t, const sph_rates &rbar_s,
+                                   const sph_adjoint &bar, hipStream_t s);
 hipError_t launch_integrate_adjoint(const Params &P, int prec, int stage, const sph_particles &p,
                                     const sph_rates &r, const double *dt, const sph_adjoint &bar,
                                     const sph_rates &rbar, double *pbar, const Workspace &ws,

@@ -1,0 +1,94 @@
+"""The pair kernel at the edges of its tiles, pages and hit lists: target
+counts around 16 (a wavefront's targets) and 64 (a workgroup's), windows of
+more sources than one page of any variant holds (at most 512) with more hits
+per target than one round of its list (64), and target lists in any order.
+
+Neighbour sets are compared exactly (tests/census.py); the pair sums of the
+variants whose pages differ from the census's with the oracle, within the
+round-off bounds of tests/gpu_helpers.py."""
+import numpy as np
+import pytest
+import torch
+
+import sph_synth as S
+from oracle import cpu
+from tests.gpu_helpers import assert_within, oracle_state, rate_bound
+from tests.test_gpu_census import check_census
+
+pytestmark = pytest.mark.gpu
+
+FP64, FP32 = 0, 1
+PRECS = [pytest.param(FP64, id="fp64"), pytest.param(FP32, id="fp32split")]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("n,box", [(1, 0.1), (15, 0.1), (16, 0.2), (17, 0.1), (63, 0.3), (64, 0.1), (65, 0.1),
+                                   (129, 1.0), (511, 0.2), (513, 0.3), (1600, 0.25)])
+def test_neighbour_sets_at_the_edges(n, box, prec):
+    """One bucket to 1,000 buckets, 1 to 1,600 particles (all in each other's window for the small boxes)."""
+    from paper_2310_03596_amd.sim import Sim
+    wl = S.random_cloud(n, seed=700 + n, h=0.05, box=box)
+    print(f"[windows] n={n} box={box} prec={prec}", flush=True)
+    sim = Sim(wl, prec)
+    sim.build()
+    cnt, chk = sim.census()
+    h = sim.A.host()
+    check_census(cnt, chk, np.arange(n), h["x"], h["x"], h["id"], wl.params["h"], prec, f"{n} in {box}")
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("pass_", [0, 1])
+def test_dense_solid_matches_oracle(pass_, prec):
+    """1,000 particles of a solid squeezed into 3^3 buckets: every window holds all of them."""
+    from paper_2310_03596_amd.sim import Sim
+    wl = S.solid_block(10, seed=701, s_sigma=1e7)
+    wl.x = wl.x.mean(0) + 0.4 * (wl.x - wl.x.mean(0))
+    print(f"[dense solid] pass={pass_} prec={prec} n={wl.n}", flush=True)
+    sim = Sim(wl, prec)
+    sim.build()
+    sim.interact(pass_=pass_)
+    torch.cuda.synchronize()
+    st = oracle_state(sim.A.host(), True)
+    start = cpu.cell_start(st.hash, cpu.ncells(wl.grid))
+    ref = cpu.interact(wl.params, wl.grid, pass_, st, st, start, True)
+    bound = rate_bound(wl.params, wl.grid, pass_, st, st, start, True, prec)
+    got = sim.rates.grad() if pass_ else sim.rates.force()
+    assert_within(got.T.cpu().numpy(), ref, bound, f"dense solid pass {pass_}")
+
+
+@pytest.mark.parametrize("prec", PRECS)
+def test_target_list_in_any_order(prec):
+    """A shuffled list (its workgroups' targets lie in many bucket rows), with
+    indices outside the array among it, over a separate source array."""
+    from paper_2310_03596_amd import _lib as L
+    from paper_2310_03596_amd.sim import SharePass
+    from paper_2310_03596_amd.state import cells_struct, stream_handle
+    loc, rem = S.c4_share("mixed", seed=702, nx=20, ny=14, nz=12, split_ix=14)
+    sp = SharePass(loc, rem, prec)
+    sp.build()
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(703)
+    pick = rng.permutation(sp.nl)[:sp.nl // 2 + 3]
+    lst = np.concatenate([pick[:100], [sp.nl, 0xFFFFFFFF], pick[100:]]).astype(np.uint32)
+    print(f"[list] prec={prec} local={sp.nl} remote={sp.nr} listed={pick.size}", flush=True)
+    dev = sp.LB.x.device
+    tidx = torch.from_numpy(lst.view(np.int32).copy()).to(dev)
+    nt = torch.tensor([lst.size], dtype=torch.int32, device=dev)
+    cnt = torch.zeros(sp.nl, dtype=torch.int32, device=dev)
+    chk = torch.zeros(sp.nl, dtype=torch.int64, device=dev)
+    L.sph_neighbor_census(sp.params, sp.grid, L.SPH_PASS_FORCE, sp.LB.struct(), tidx.data_ptr(), nt.data_ptr(),
+                          sp.RB.struct(), cells_struct(sp.rstart, sp.nc), cnt.data_ptr(), chk.data_ptr(),
+                          sp.ws.data_ptr(), sp.ws_bytes, stream_handle())
+    torch.cuda.synchronize()
+    hl, hr = sp.LB.host(), sp.RB.host()
+    c, k = cnt.cpu().numpy().view(np.uint32), chk.cpu().numpy().view(np.uint64)
+    t = np.sort(pick)
+    check_census(c, k, t, hl["x"][t], hr["x"], hr["id"], loc.params["h"], prec, "shuffled list")
+    off = np.setdiff1d(np.arange(sp.nl), pick)
+    assert not c[off].any() and not k[off].any()
