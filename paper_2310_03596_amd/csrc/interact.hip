@@ -9,19 +9,21 @@
 // consecutive targets, in groups that share a bucket row (cy, cz); consecutive
 // sorted targets almost always do.
 //   * The window of a group is the 9 neighbour rows over the union of its
-//     targets' buckets, about a thousand sources on a lattice.  The workgroup
-//     loads it once, coalesced, straight from the particle fields, and keeps
-//     the whole records in LDS (in pages when it is longer than one).
+//     targets' buckets, about 800 sources on a lattice.  The workgroup first
+//     reads their positions and culls those that are farther than 2h from the
+//     box of its targets (435 remain of a lattice's, 600 of a disordered
+//     fluid's), then loads the others once, straight from the particle fields,
+//     and keeps the whole records in LDS (in pages when they fill more than one).
 //   * Each wavefront takes 16 of the targets.  The candidate test of 16
 //     sources against 16 targets is one matrix product (K = 4) on the matrix
 //     cores, with the test's bound as its initial value, so the sign of each
 //     result is the answer and one instruction per result collects the signs
 //     in a bit mask per lane.
 //   * The hits of a target go to its list in LDS, and four lanes share the
-//     list evenly: only ~1 candidate in 14 of the window is a neighbour, so the
-//     cheap test and the pair body (about a hundred operations) are kept
-//     apart, and the body runs dense.  (One lane per target would leave the
-//     chip idle below some 60,000 particles, and wait for its busiest lane.)
+//     list evenly: only ~1 candidate in 6 is a neighbour, so the cheap test
+//     and the pair body (about a hundred operations) are kept apart, and the
+//     body runs dense.  (One lane per target would leave the chip idle below
+//     some 60,000 particles, and wait for its busiest lane.)
 // The four lanes' sums are added at the end.  The order of summation depends
 // on the particles' order alone, so repeated calls agree bit for bit.  A pair
 // with r = 0 (the target itself, or a coincident particle) adds nothing: its
@@ -31,17 +33,23 @@
 // side >= 2h on some axis and fails the pair body's distance test, so testing
 // the group's whole window changes no neighbour set.
 //
-// What bounds it: vector-instruction issue.  On the 810,448-particle column a
-// wavefront issues about 3,600 vector instructions, 2,300 of them in the pair
-// body; its time without the body is 0.17 of 0.40 ms (FP32).  Hits read from
-// L1 instead (one lane per target, three to ten 16-byte reads per hit that
-// touch a line each) held the vector units back: L1 lookups took 76 % (FP32) to
-// 100 % (FP64) of such a kernel's cycles.  Measured per pass, the reads from L1
-// with their staging kernel before, this kernel now: column FORCE FP32 401 ->
-// 391 us, FP64 675 -> 572; 4.0 M cylinder (FP32) FORCE 2.89 -> 2.59 ms,
-// GRADIENT 1.62 -> 1.50; 6.7 M impact (FP64) FORCE 8.83 -> 6.53 ms, GRADIENT
-// 4.02 -> 3.04; 250,047-particle FORCE reverse FP32 260 -> 248 us; 27,000 ones
-// FP64 FORCE 54 -> 44 us; 8,000 ones FP32 63 -> 32 us.
+// What bounds it: vector-instruction issue.  On the 810,448-particle column
+// (FP32) a wavefront issues about 3,600 vector instructions, 2,100 of them in
+// the pair body, and the vector units are busy for three quarters of the
+// pass.  Hits read from L1 instead of LDS (one lane per target, three to ten
+// 16-byte reads per hit that touch a line each) held the vector units back: L1
+// lookups took 76 % (FP32) to 100 % (FP64) of such a kernel's cycles.  Culling
+// brings the records of a group down to one page or two, so that fewer targets
+// wait for the one with the most hits in a page (22 rounds of the body per
+// wavefront instead of 26; 20.25 if no lane ever waited).  Measured per pass,
+// reads from L1 with their staging kernel first, whole windows in LDS second,
+// culled ones third: column FORCE FP32 401, 391, 350 us, FP64 675, 572, 520;
+// 4.0 M cylinder (FP32) FORCE 2.89, 2.59, 2.39 ms, GRADIENT 1.62, 1.50, 1.31;
+// 6.7 M impact (FP64) FORCE 8.83, 6.53, 6.15 ms, GRADIENT 4.02, 3.04, 2.80;
+// 250,047-particle FORCE reverse FP32 260, 248, 233 us; 27,000 ones FP64 FORCE
+// 54, 43, 39 us; 8,000 ones FP32 63, 33, 28 us.  Culling and loading in one
+// sweep instead of two was slower (441 us for the column's 373): each
+// source's fields then wait for its position.
 //
 // In the FP32-split form the position difference is rebuilt from bucket
 // indices and float offsets, d = (c_j - c_i) L + (off_j - off_i), which is
@@ -65,6 +73,13 @@ constexpr int kPairWaves = 4;                     // wavefronts per workgroup
 constexpr int kPairBlock = kPairWaves * kWave;    // threads per workgroup
 constexpr int kGroup = kPairWaves * kTile;        // targets per workgroup (one per lane of a wavefront)
 constexpr int kShare = kWave / kTile;             // lanes that share a target
+// Sources in flight per lane while the window is culled (column FP32: 1 364,
+// 2 362, 4 368 us).
+constexpr int kAhead = 2;
+constexpr int kSeg = 384;                         // entries of a batch that a wavefront looks at
+constexpr int kBatch = kPairWaves * kSeg;         // window entries culled at a time (a lattice's windows: 800 to 1,450)
+constexpr int kEntryBits = 11;                    // of a kept entry's code: its place in the batch, then its row
+static_assert(kBatch <= 1 << kEntryBits && kSeg % (kWave * kAhead) == 0, "a batch's entries");
 static_assert(kGroup == kWave, "lane l of every wavefront looks at target l of the workgroup");
 constexpr int kPassAdjoint = 2;            // reverse mode of the FORCE pass
 constexpr int kPassGradAdjoint = 4;        // reverse mode of the GRADIENT pass
@@ -109,11 +124,11 @@ struct Pass {
     static constexpr bool HALF = REST > 0 && 2 * REST <= C;
     static constexpr int NV = NR / C + (REST > 0 && !HALF ? 1 : 0);
     // Wavefronts per SIMD: caps the registers at 512 / that and the LDS of a
-    // workgroup at 160 KB / that.  The most at which nothing (FP64 fluid
-    // FORCE: 14 registers outside the pair loop) is spilled: one more is
-    // slower by 20 to 80 % (solid FORCE FP64 6.5 -> 12.2 ms, FP32 adjoint 278
-    // -> 502 us), one fewer by 4 to 30 %, as a page holds more but fewer
-    // wavefronts hide each other's waits.
+    // workgroup at 160 KB / that (LDS is given out in 1,280 bytes).  The most
+    // at which next to nothing is spilled (two registers; FP32 adjoint nine):
+    // one more is slower by 20 to 80 % (solid FORCE FP64 6.5 -> 12.2 ms, FP32
+    // adjoint 278 -> 502 us), one fewer by 2 to 30 %, as a page holds more but
+    // fewer wavefronts hide each other's waits.
     static constexpr int waves_f32 = ADJ ? (SOLID ? 2 : 3) : (GADJ || (FORCE && SOLID) ? 3 : 4);
     static constexpr int waves_f64 = ADJ ? (SOLID ? 1 : 2) : (GADJ || (FORCE && SOLID) ? 2 : 3);
     static constexpr int waves = SPLIT ? waves_f32 : waves_f64;
@@ -123,13 +138,23 @@ struct Pass {
     // with two, 397 with one; FP64 598 and 563; FP32 adjoint 277 and 250; but
     // GRADIENT FP32 1,498 and 1,537, solid FORCE FP64 6,570 and 6,650).
     static constexpr bool kTwoAhead = GRAD || GADJ || (FORCE && SOLID);
-    static constexpr int kCap = 64;   // listed hits per target and round
+    // Listed hits per target and round: above the 81 (and near misses) of a
+    // lattice at h = 1.3 dx, since all may be in one page and a second round
+    // lists them by a slower loop (64: column FP64 523 us, 8,000 FP32 particles
+    // 32; 96: 515 and 28; 112 leaves less room for the page: 536 and 29.5).
+    static constexpr int kCap = 96;
     // A page is laid out as kRows rows of up to kPlaces sources, as many as the
-    // LDS has room for (16 rows measured better than 20 to 32, whose bit-mask
-    // words hold fewer hits each).  Rows start in different LDS banks (odd
+    // LDS has room for (up to 20 rows: a page of 16 held GRADIENT at 1.38 ms for
+    // 1.31; with 24 its lists and words cost more than the page gains).  The
+    // hit lists take the place of the candidate operands once these have been
+    // read, which is worth a barrier: one page holds 440 sources instead of 336
+    // (column FP32 352 -> 344 us).  Rows start in different LDS banks (odd
     // pitch), and so do the candidate operands that 16 lanes read together
     // (pitch 4 or 12 modulo 16).
-    static constexpr int kBudget = 160 * 1024 / waves - kGroup * (kCap + 2) * 2 - 512;
+    static constexpr int kBudget = 128 / waves * 1280 - kBatch * 2 - 128;
+    static constexpr int kListPitch = kCap + 2;   // (+ 2: the rows start in different banks)
+    static constexpr int kListBytes = kGroup * kListPitch * 2 + 64;
+    static constexpr int most_of(int a, int b) { return a > b ? a : b; }
     static constexpr int REC = 16 * NV + (HALF ? 8 : 0);
     static constexpr int up4(int places) { return (places + 3) / 4 * 4; }
     static constexpr int pitch_of(int places) { return places | 1; }
@@ -137,19 +162,20 @@ struct Pass {
     static constexpr int places_of(int rows)
     {
         int p = 32;   // a row's hits fit one word
-        while (p > 0 && rows * (pitch_of(p) * REC + cand_pitch_of(p) * 16) > kBudget) --p;
+        while (p > 0 && rows * pitch_of(p) * REC + most_of(rows * cand_pitch_of(p) * 16, kListBytes) > kBudget) --p;
         return p;
     }
     static constexpr int best_rows()
     {
         int best = 4;
-        for (int r = 4; r <= 16; r += 4)
+        for (int r = 4; r <= 20; r += 4)
             if (r * places_of(r) > best * places_of(best)) best = r;
         return best;
     }
     static constexpr int kRows = best_rows(), kPlaces = places_of(kRows);
     static constexpr int kPitch = pitch_of(kPlaces), kCandPitch = cand_pitch_of(kPlaces);
     static constexpr int kPage = kRows * kPlaces;
+    static constexpr int kShared = most_of(kRows * kCandPitch * 16, kListBytes);
     static_assert(kPage >= 128, "a page");
 };
 
@@ -199,21 +225,6 @@ __device__ inline int dpp(int own, int v)
     return __builtin_amdgcn_update_dpp(own, v, CTRL, ROWS, 0xF, false);
 }
 
-// Smallest value over the wavefront, by data-parallel moves: towards the last
-// lane of each row of 16, then over the rows.
-__device__ inline int wave_min(int v)
-{
-    const int none = 0x7FFFFFFF;
-    v = min(v, dpp<0x111>(none, v));        // from the lane 1 before
-    v = min(v, dpp<0x112>(none, v));
-    v = min(v, dpp<0x114>(none, v));
-    v = min(v, dpp<0x118>(none, v));
-    v = min(v, dpp<0x142, 0xA>(none, v));   // the row before, into rows 1 and 3
-    v = min(v, dpp<0x143, 0xC>(none, v));   // row 1, into rows 2 and 3
-    return __builtin_amdgcn_readlane(v, kWave - 1);
-}
-__device__ inline int wave_max(int v) { return ~wave_min(~v); }   // ~ reverses the order
-
 // Largest value over the wavefront of a v in [0, 128), by seven ballots (no
 // cross-lane data movement).
 __device__ inline int wave_max_u7(int v)
@@ -225,6 +236,38 @@ __device__ inline int wave_max_u7(int v)
         if (__ballot(v >= c)) r = c;
     }
     return r;
+}
+
+// The largest values over the wavefront of four unsigned numbers, in place:
+// two exchanges of half wavefronts and one of rows of 16 lanes leave one
+// number to a row, whose lanes then fold towards the last.
+__device__ inline void wave_max4(uint32_t v[4])
+{
+    uint32_t m[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto s = __builtin_amdgcn_permlane32_swap(v[k], v[k + 2], false, false);
+        m[k] = max(s[0], s[1]);   // v[k] in the lower half, v[k + 2] in the upper one
+    }
+    const auto s = __builtin_amdgcn_permlane16_swap(m[0], m[1], false, false);
+    uint32_t a = max(s[0], s[1]);   // rows: v[0], v[1], v[2], v[3]
+    a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x111, 0xF, 0xF, true));
+    a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x112, 0xF, 0xF, true));
+    a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x114, 0xF, 0xF, true));
+    a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x118, 0xF, 0xF, true));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_readlane(a, 16 * k + 15);
+}
+
+// Floats as unsigned integers of the same order, and back.
+__device__ inline uint32_t ordered(float v)
+{
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    return b ^ ((uint32_t)((int)b >> 31) | 0x80000000u);
+}
+__device__ inline float unordered(uint32_t u)
+{
+    return __builtin_bit_cast(float, u ^ (~(uint32_t)((int)u >> 31) | 0x80000000u));
 }
 
 // The sum of v over the four lanes 4 k .. 4 k + 3, in each of them.
@@ -316,10 +359,18 @@ __device__ inline void load_fields(const PV<real> &s, const RV<real> &rb, const 
     }
 }
 
+// Constants of a pass, made on the host so that they are scalar operands.
+template <typename real>
+struct PairArgs {
+    PairK<real> K;
+    real R2;    // (2h)^2
+    float h2;   // 2h
+};
+
 template <typename real, int PASS, bool SOLID>
 __global__ __launch_bounds__(kPairBlock)
 __attribute__((amdgpu_waves_per_eu(Pass<real, PASS, SOLID>::waves)))
-void k_pairs(Params P, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, const uint32_t *__restrict__ ntdev,
+void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, const uint32_t *__restrict__ ntdev,
              PV<real> src, const uint32_t *__restrict__ sstart, int zero_first, RV<real> R, RV<real> Rsrc, AV<real> B,
              Census cz)
 {
@@ -332,8 +383,13 @@ void k_pairs(Params P, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, c
     using half = typename Chunk<real>::half;
     __shared__ full plane[W::NV][kRows * kPitch];
     __shared__ half plane_h[W::HALF ? kRows * kPitch : 1];
-    __shared__ f32x4 cand[kRows * kCandPitch];            // (q, |q|^2) of the page's sources
-    __shared__ uint16_t list[kPairWaves][kTile][kCap + 2];   // (+ 2: the rows start in different banks)
+    // the candidate operands (q, |q|^2) of the page's sources, then the hit lists
+    __shared__ alignas(16) unsigned char shared[W::kShared];
+    f32x4 *const cand = reinterpret_cast<f32x4 *>(shared);
+    uint16_t *const list = reinterpret_cast<uint16_t *>(shared);
+    __shared__ uint16_t kept_of[kBatch];                  // the window's entries near the group, a segment per wavefront
+    __shared__ uint32_t kept_n[kPairWaves];
+    constexpr int kListPitch = W::kListPitch;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     uint32_t nt = tg.n, tile;
@@ -362,8 +418,8 @@ void k_pairs(Params P, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, c
     uint64_t pending = __ballot(tvalid);
     const bool valid = (pending >> le) & 1ull;
 
-    const PairK<real> K = make_pair_k<real>(P);
-    const real R2 = (real)P.R2;
+    const PairK<real> &K = A.K;
+    const real R2 = A.R2;
 
     TargetPos<real> T;
     T.Lf = SPLIT ? (real)g.Lf : real(0);
@@ -498,7 +554,6 @@ void k_pairs(Params P, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, c
     constexpr int kRec = W::NV * C + (W::HALF ? C / 2 : 0);
     const float kFar = 1e30f;
 
-    bool fresh = true;   // no page has been read yet
     while (pending) {
         // the next group: targets that share the first pending target's bucket row
         const int leader = __ffsll((unsigned long long)pending) - 1;
@@ -506,52 +561,74 @@ void k_pairs(Params P, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, c
         const bool tin = tvalid && trow == key;
         const uint64_t in64 = __ballot(tin);
         pending &= ~in64;
-        const int gx0 = wave_min(tin ? tcx : 0x7FFFFFFF);
-        const int gx1 = wave_max(tin ? tcx : (int)0x80000000);
+        const int lcx = __builtin_amdgcn_readlane(tcx, leader);   // origin of the group's frame along x
         const int gz = (int)(key / (uint32_t)g.ny), gy = (int)(key - (uint32_t)gz * (uint32_t)g.ny);
         const bool fin = (in64 >> lf) & 1ull;
         const uint32_t in_tile = (uint32_t)(in64 >> (wave * kTile)) & 0xFFFFu;
-        T.cxf = (real)(ecx - gx0);
+        T.cxf = (real)(ecx - lcx);
         // Frame of the candidate test, in FP32 in both forms: positions relative
-        // to the corner of bucket (gx0, gy, gz); split form ((c - gx0) L + off)
+        // to the corner of bucket (lcx, gy, gz); split form ((c - lcx) L + off)
         // in x and (dy L + off) in y, z; FP64 form (x - corner) in FP64, rounded
         // once to float.  The test is the expanded form
-        // |q|^2 - 2 q.f < R2 - |f|^2.  For a candidate within 2h of the target (|q| <= |f| + 2h) its rounding, with that of
-        // the frame, stays below 2^-18 (|f| + 2h)^2; the bound is widened by
-        // four times that, and in FP64 also by 2^-46 X (|f| + 2h) with
-        // X = |corner|_1 + |f| + 2h, over ten times the rounding of the FP64
-        // differences.  So the listed candidates hold every neighbour.  The
-        // pair body applies the neighbour predicate itself, on the exact, odd d.
-        float fo[3];
+        // |q|^2 - 2 q.f < R2 - |f|^2.  For a candidate within 2h of the target
+        // (|q| <= |f| + 2h) its rounding, with that of the frame, stays below
+        // 2^-18 (|f| + 2h)^2; the bound is widened by four times that, and in
+        // FP64 also by 2^-46 X (|f| + 2h) with X = |corner|_1 + |f| + 2h, over
+        // ten times the rounding of the FP64 differences.  So the listed
+        // candidates hold every neighbour.  The pair body applies the neighbour
+        // predicate itself, on the exact, odd d.
+        uint32_t ext[8];
+        float lo[3], hi[3], fo[3];   // the box of the group's targets, and the lane's target of the test
         double corner[3] = {0.0, 0.0, 0.0};
-        const int fcx = __shfl(tcx, lf, kWave);
-        const uint32_t fi = __shfl(ti, lf, kWave);
-        real fpos[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            if constexpr (SPLIT)
-                fpos[d] = tg.off[d][fi];
-            else
-                fpos[d] = tg.x[d][fi];
-        }
-        if constexpr (SPLIT) {
-            fo[0] = (real)(fcx - gx0) * T.Lf + fpos[0];
-            fo[1] = fpos[1];
-            fo[2] = fpos[2];
-        } else {
-            corner[0] = uniform_double(g.o[0] + (double)gx0 * g.L);
+        if constexpr (!SPLIT) {
+            corner[0] = uniform_double(g.o[0] + (double)lcx * g.L);
             corner[1] = uniform_double(g.o[1] + (double)gy * g.L);
             corner[2] = uniform_double(g.o[2] + (double)gz * g.L);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) fo[d] = (float)(fpos[d] - corner[d]);
         }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            float at;
+            if constexpr (SPLIT)
+                at = d == 0 ? (real)(tcx - lcx) * T.Lf + tg.off[d][ti] : tg.off[d][ti];
+            else
+                at = (float)(tg.x[d][ti] - corner[d]);
+            const uint32_t o = ordered(at);
+            ext[2 * d] = tin ? o : 0u;
+            ext[2 * d + 1] = tin ? ~o : 0u;
+            fo[d] = __shfl(at, lf, kWave);
+        }
+        ext[6] = tin ? (uint32_t)tcx : 0u;
+        ext[7] = tin ? ~(uint32_t)tcx : 0u;
+        wave_max4(ext);
+        wave_max4(ext + 4);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            hi[d] = unordered(ext[2 * d]);
+            lo[d] = unordered(~ext[2 * d + 1]);
+        }
+        const int gx1 = (int)ext[6], gx0 = (int)~ext[7];   // the targets' buckets
         const float f2 = fo[0] * fo[0] + fo[1] * fo[1] + fo[2] * fo[2];
-        const float fl = sqrtf(f2) + (float)(2.0 * P.h);
+        const float fl = __builtin_amdgcn_sqrtf(f2) + A.h2;
         float margin = 0x1p-16f * fl * fl;
         if constexpr (!SPLIT) {
             const float X = (float)(fabs(corner[0]) + fabs(corner[1]) + fabs(corner[2])) + fl;
             margin += 0x1p-46f * X * fl;
         }
+        // Sources within 2h of a target lie within 2h of the targets' box, up to
+        // the same rounding (a NaN keeps every source).
+        float b2 = 0.0f;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const float m = fmaxf(fabsf(lo[d]), fabsf(hi[d]));
+            b2 += m * m;
+        }
+        const float bl = __builtin_amdgcn_sqrtf(b2) + A.h2;
+        float bmargin = 0x1p-16f * bl * bl;
+        if constexpr (!SPLIT) {
+            const float X = (float)(fabs(corner[0]) + fabs(corner[1]) + fabs(corner[2])) + bl;
+            bmargin += 0x1p-46f * X * bl;
+        }
+        const float bbound = (float)R2 + bmargin;
         // the product starts at minus the bound: its sign bit is the answer
         const float c0 = fin ? -(((float)R2 - f2) + margin) : kFar;
         const f32x4 cinit = {c0, c0, c0, c0};
@@ -578,193 +655,254 @@ void k_pairs(Params P, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, c
         const uint32_t total = __builtin_amdgcn_readlane(woff, 8);
         woff -= wn;
         const uint32_t wdel = wub - woff;
-        const uint64_t wrows = __ballot(wn > 0);   // rows with sources
-        // page p of the window takes its entries p, p + npages, ..., so that
-        // every page holds an even share of each target's hits
-        const uint32_t npages = (total + kPage - 1) / kPage;
-        const uint32_t hash0 = key * (uint32_t)g.nx + (uint32_t)gx0;   // of bucket (gx0, gy, gz)
-        for (uint32_t page = 0; page < npages; ++page) {
-            const uint32_t len = (total - page + npages - 1) / npages;
-            const uint32_t blocks = (len + 4 * kRows - 1) / (4 * kRows);   // of four places of every row
-            if (!fresh) __syncthreads();   // every read of the page before is done
-            fresh = false;
-            // Entry u of the page goes to place u / kRows of row u % kRows: a row,
-            // which one lane's word of hit bits covers, samples the page
-            // evenly, so that the words of a target hold similar numbers of hits.
-            // One source per thread at a time (two or three in flight cost
-            // spills: impact FORCE 6.5 -> 8.9 ms, FP32 adjoint 278 -> 366 us).
-            const uint32_t ends = blocks * (4 * kRows);
+        const uint32_t hash0 = key * (uint32_t)g.nx + (uint32_t)lcx;   // of bucket (lcx, gy, gz)
+        const int rz = (lane * 11) >> 5;
+        // hash of bucket lcx of row `lane` of the window
+        const uint32_t rhash = hash0 + (uint32_t)g.nx * ((uint32_t)(lane - 3 * rz - 1) + (uint32_t)g.ny * (uint32_t)(rz - 1));
+        // a source's position in the frame of the candidate test
+        auto framed = [&](const real *q, real dcx, real ddy, real ddz) {
+            f32x4 a;
+            if constexpr (SPLIT) {
+                a.x = dcx * T.Lf + q[0];
+                a.y = ddy + q[1];
+                a.z = ddz + q[2];
+            } else {
+                a.x = (float)(q[0] - corner[0]);
+                a.y = (float)(q[1] - corner[1]);
+                a.z = (float)(q[2] - corner[2]);
+            }
+            return a;
+        };
+        uint32_t off[9];   // of the rows, in scalar registers
+#pragma unroll
+        for (int r = 1; r < 9; ++r) off[r] = __builtin_amdgcn_readlane(woff, r);
+        for (uint32_t batch = 0; batch < total; batch += kBatch) {
+            // The batch's sources that are near no target are culled before their
+            // records are read.  Each wavefront looks at every fourth piece of 64
+            // entries, several pieces in flight, and lists what it keeps.
+            const uint32_t bend = min(total - batch, (uint32_t)kBatch) + batch;
+            uint32_t n = 0;
+            for (uint32_t w0 = batch + (uint32_t)(wave * kWave); w0 < bend; w0 += kAhead * kPairBlock) {
+                real q[kAhead][3];
+                uint32_t row[kAhead], hs[kAhead];
+#pragma unroll
+                for (int a = 0; a < kAhead; ++a) {
+                    const uint32_t u = min(w0 + (uint32_t)(a * kPairBlock + lane), bend - 1);
+                    int r = 0;
+#pragma unroll
+                    for (int k = 1; k < 9; ++k) r += u >= off[k] ? 1 : 0;
+                    const uint32_t j = u + __shfl(wdel, r, kWave);
+                    row[a] = r;
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) q[a][d] = SPLIT ? field(src.off[d], j) : (real)field(src.x[d], j);
+                    if constexpr (SPLIT) hs[a] = field(src.hash, j);
+                }
+#pragma unroll
+                for (int a = 0; a < kAhead; ++a) {
+                    if (a && w0 + a * kPairBlock >= bend) break;
+                    real dcx = 0, ddy = 0, ddz = 0;
+                    if constexpr (SPLIT) {
+                        dcx = (real)(int)(hs[a] - __shfl(rhash, row[a], kWave));
+                        const int z = (int)(row[a] * 11) >> 5;
+                        ddy = (real)((int)row[a] - 3 * z - 1) * T.Lf;
+                        ddz = (real)(z - 1) * T.Lf;
+                    }
+                    const f32x4 at = framed(q[a], dcx, ddy, ddz);
+                    // distances from the box along each axis
+                    const float ex = fmaxf(fmaxf(lo[0] - at.x, at.x - hi[0]), 0.0f);
+                    const float ey = fmaxf(fmaxf(lo[1] - at.y, at.y - hi[1]), 0.0f);
+                    const float ez = fmaxf(fmaxf(lo[2] - at.z, at.z - hi[2]), 0.0f);
+                    const uint32_t u = w0 + (uint32_t)(a * kPairBlock + lane);
+                    const bool keep = u < bend && !(ex * ex + ey * ey + ez * ez > bbound);
+                    const uint64_t mask = __ballot(keep);
+                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                    if (keep) kept_of[(uint32_t)(wave * kSeg) + n + rank] = (uint16_t)(row[a] << kEntryBits | (u - batch));
+                    n += (uint32_t)__popcll(mask);
+                }
+            }
+            if (lane == 0) kept_n[wave] = n;
+            __syncthreads();   // the kept entries are listed, and every read of the page before is done
+            uint32_t kept = 0, seg0[kPairWaves], jump[kPairWaves];
+#pragma unroll
+            for (int w = 0; w < kPairWaves; ++w) {
+                const uint32_t n = __builtin_amdgcn_readfirstlane(kept_n[w]);
+                seg0[w] = kept;
+                kept += n;
+                jump[w] = (uint32_t)kSeg - n;   // from the end of the segment to the next one
+            }
+            // page p takes the kept entries p, p + npages, ..., so that every page
+            // holds an even share of each target's hits
+            const uint32_t npages = (kept + kPage - 1) / kPage;
+            if (npages == 0) __syncthreads();   // every read of kept_n is done
+            for (uint32_t page = 0; page < npages; ++page) {
+                const uint32_t len = (kept - page + npages - 1) / npages;
+                const uint32_t blocks = (len + 4 * kRows - 1) / (4 * kRows);   // of four places of every row
+                if (page) __syncthreads();   // every read of the page before is done
+                // Entry u of the page goes to place u / kRows of row u % kRows: a row,
+                // which one lane's word of hit bits covers, samples the page
+                // evenly, so that the words of a target hold similar numbers of hits.
+                // One source per thread at a time (two or three in flight cost
+                // spills: impact FORCE 6.5 -> 8.9 ms, FP32 adjoint 278 -> 366 us).
+                // Blocks need not end where 64 lanes do: what lies past the last
+                // one has no place.
+                const uint32_t ends = blocks * (4 * kRows);
 #pragma unroll 1
-            for (uint32_t w0 = (uint32_t)(wave * kWave); w0 < ends; w0 += kPairBlock) {
-                const uint32_t u = w0 + (uint32_t)lane;
-                const uint32_t uw0 = w0 * npages + page, uw = uw0 + (uint32_t)lane * npages;   // entries of the window
-                // the window's rows that the wavefront's entries meet
-                uint64_t meet = wrows & __ballot(lane < 9 && woff < uw0 + kWave * npages && woff + wn > uw0);
-                uint32_t del = 0;
-                int dy = 0, dz = 0;
-                while (meet) {
-                    const int r = __ffsll((unsigned long long)meet) - 1;
-                    meet &= meet - 1;
-                    const uint32_t o = __builtin_amdgcn_readlane(woff, r), e = __builtin_amdgcn_readlane(wdel, r);
-                    const int rz = (r * 11) >> 5;
-                    const bool past = uw >= o;
-                    del = past ? e : del;
-                    dy = past ? r - 3 * rz - 1 : dy;
-                    dz = past ? rz - 1 : dz;
+                for (uint32_t w0 = (uint32_t)(wave * kWave); w0 < ends; w0 += kPairBlock) {
+                    const uint32_t u = w0 + (uint32_t)lane;
+                    const uint32_t v = min(u, len - 1) * npages + page;   // of the kept entries
+                    uint32_t at = v;
+#pragma unroll
+                    for (int w = 1; w < kPairWaves; ++w) at += v >= seg0[w] ? jump[w - 1] : 0u;
+                    const uint32_t code = kept_of[at];
+                    const int r = (int)(code >> kEntryBits);
+                    const uint32_t j = batch + (code & ((1u << kEntryBits) - 1u)) + __shfl(wdel, r, kWave);
+                    const uint32_t hr = SPLIT ? __shfl(rhash, r, kWave) : 0u;
+                    const uint32_t place = u / (uint32_t)kRows, row = u % (uint32_t)kRows;
+                    f32x4 a = {0.0f, 0.0f, 0.0f, kFar};   // past the page's end: no target takes it
+                    if (u < len) {
+                        real q[W::NR];
+                        if constexpr (SPLIT) {
+#pragma unroll
+                            for (int d = 0; d < 3; ++d) q[d] = field(src.off[d], j);
+                            q[3] = (real)(int)(field(src.hash, j) - hr);
+                            const int z = (r * 11) >> 5;
+                            q[W::NR - 2] = (real)(r - 3 * z - 1) * T.Lf;
+                            q[W::NR - 1] = (real)(z - 1) * T.Lf;
+                        } else {
+#pragma unroll
+                            for (int d = 0; d < 3; ++d) q[d] = field(src.x[d], j);
+                        }
+                        load_fields<real, PASS, SOLID>(src, Rsrc, cz, j, q + W::NPOS);
+                        a = framed(q, q[3], q[W::NR - 2], q[W::NR - 1]);
+                        a.w = a.x * a.x + a.y * a.y + a.z * a.z;
+                        const uint32_t k = row * (uint32_t)kPitch + place;
+#pragma unroll
+                        for (int c = 0; c < W::NV; ++c) {
+                            full v;
+#pragma unroll
+                            for (int e = 0; e < C; ++e) v[e] = c * C + e < W::NR ? q[c * C + e] : real(0);
+                            plane[c][k] = v;
+                        }
+                        if constexpr (W::HALF) {
+                            half v;
+#pragma unroll
+                            for (int e = 0; e < C / 2; ++e) v[e] = W::NV * C + e < W::NR ? q[W::NV * C + e] : real(0);
+                            plane_h[k] = v;
+                        }
+                    }
+                    if (u < ends) cand[row * (uint32_t)kCandPitch + place] = a;
                 }
-                const uint32_t place = u / (uint32_t)kRows, row = u % (uint32_t)kRows;
-                f32x4 a = {0.0f, 0.0f, 0.0f, kFar};   // past the page's end: no target takes it
-                if (u < len) {
-                    const uint32_t j = uw + del;
-                    real q[W::NR];
-                    if constexpr (SPLIT) {
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) q[d] = field(src.off[d], j);
-                        // hash of the source less that of bucket (gx0, y, z)
-                        const uint32_t hr = hash0 + (uint32_t)g.nx * ((uint32_t)dy + (uint32_t)g.ny * (uint32_t)dz);
-                        q[3] = (real)(int)(field(src.hash, j) - hr);
-                        q[W::NR - 2] = (real)dy * T.Lf;
-                        q[W::NR - 1] = (real)dz * T.Lf;
-                    } else {
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) q[d] = field(src.x[d], j);
-                    }
-                    load_fields<real, PASS, SOLID>(src, Rsrc, cz, j, q + W::NPOS);
-                    if constexpr (SPLIT) {
-                        a.x = q[3] * T.Lf + q[0];
-                        a.y = q[W::NR - 2] + q[1];
-                        a.z = q[W::NR - 1] + q[2];
-                    } else {
-                        a.x = (float)(q[0] - corner[0]);
-                        a.y = (float)(q[1] - corner[1]);
-                        a.z = (float)(q[2] - corner[2]);
-                    }
-                    a.w = a.x * a.x + a.y * a.y + a.z * a.z;
-                    const uint32_t k = row * (uint32_t)kPitch + place;
-#pragma unroll
-                    for (int c = 0; c < W::NV; ++c) {
-                        full v;
-#pragma unroll
-                        for (int e = 0; e < C; ++e) v[e] = c * C + e < W::NR ? q[c * C + e] : real(0);
-                        plane[c][k] = v;
-                    }
-                    if constexpr (W::HALF) {
-                        half v;
-#pragma unroll
-                        for (int e = 0; e < C / 2; ++e) v[e] = W::NV * C + e < W::NR ? q[W::NV * C + e] : real(0);
-                        plane_h[k] = v;
-                    }
-                }
-                cand[row * (uint32_t)kCandPitch + place] = a;
-            }
-            __syncthreads();
-            if (!in_tile) continue;
+                __syncthreads();
 
-            // The candidate test, 16 entries x 16 targets at a time: block m of
-            // rows 4 k .. 4 k + 3 takes their places 4 m .. 4 m + 3, lane l
-            // receives the values of row 4 k + l / 16 for target l % 16 and
-            // shifts their signs into word k, place 0 highest.
-            uint32_t word[kWords];
-            const float *pa = reinterpret_cast<const float *>(cand + ((lane & 15) >> 2) * kCandPitch + (lane & 3)) + quarter;
+                // The candidate test, 16 entries x 16 targets at a time: block m of
+                // rows 4 k .. 4 k + 3 takes their places 4 m .. 4 m + 3, lane l
+                // receives the values of row 4 k + l / 16 for target l % 16 and
+                // shifts their signs into word k, place 0 highest.
+                uint32_t word[kWords];
+                const float *pa = reinterpret_cast<const float *>(cand + ((lane & 15) >> 2) * kCandPitch + (lane & 3)) + quarter;
 #pragma unroll
-            for (int k = 0; k < kWords; ++k) word[k] = 0;
-            float aop[kWords];
+                for (int k = 0; k < kWords; ++k) word[k] = 0;
+                float aop[kWords];
 #pragma unroll
-            for (int k = 0; k < kWords; ++k) aop[k] = pa[k * 4 * kCandPitch * 4];
-            for (uint32_t m = 1; m <= blocks; ++m) {
-                f32x4 c[kWords];
+                for (int k = 0; k < kWords; ++k) aop[k] = pa[k * 4 * kCandPitch * 4];
+                for (uint32_t m = in_tile ? 1 : blocks + 1; m <= blocks; ++m) {
+                    f32x4 c[kWords];
 #pragma unroll
-                for (int k = 0; k < kWords; ++k) c[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop[k], bop, cinit, 0, 0, 0);
-                if (m < blocks) {   // the next block's operands
-                    pa += 16;
+                    for (int k = 0; k < kWords; ++k) c[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop[k], bop, cinit, 0, 0, 0);
+                    if (m < blocks) {   // the next block's operands
+                        pa += 16;
 #pragma unroll
-                    for (int k = 0; k < kWords; ++k) aop[k] = pa[k * 4 * kCandPitch * 4];
-                }
-#pragma unroll
-                for (int k = 0; k < kWords; ++k)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float v = c[k][e];
-                        word[k] = __builtin_amdgcn_alignbit(word[k], __builtin_bit_cast(uint32_t, v), 31);
+                        for (int k = 0; k < kWords; ++k) aop[k] = pa[k * 4 * kCandPitch * 4];
                     }
-            }
-            int own = 0;
 #pragma unroll
-            for (int k = 0; k < kWords; ++k) own += __popc(word[k]);
-            const uint32_t top = 4 * blocks - 1;   // place 0's bit
-            // the four lanes of a target list their hits one lane after the other
-            const int own16 = __shfl_xor(own, 16, kWave);
-            const int two = own + own16, two32 = __shfl_xor(two, 32, kWave);
-            const int before = ((quarter & 1) ? own16 : 0) + ((quarter & 2) ? two32 : 0);
-            const int all = two + two32;
-            const int mine = __shfl(all, lane / kShare, kWave);   // of the target the lane evaluates
-            // rounds of up to kCap listed hits per target (one, unless the
-            // particles are far denser than a lattice)
-            const bool fits = !__ballot(all > kCap);
-            for (int done = 0; __ballot(all > done); done += kCap) {
-                uint16_t *to = list[wave][lane & (kTile - 1)];
-                int pos = before - done;
+                    for (int k = 0; k < kWords; ++k)
 #pragma unroll
-                for (int k = 0; k < kWords; ++k) {
-                    // a bit b stands for the source in slot last - b
-                    const uint32_t last = (uint32_t)((4 * k + quarter) * kPitch) + top;
-                    uint32_t w = word[k];
-                    if (fits) {
-                        // a word's hits from both ends at once; the last of an
-                        // odd number is written twice, to the same place
-                        uint16_t *lo = to + pos, *hi = to + (pos += __popc(w)) - 1;
-                        while (w) {
-                            const int a = __builtin_clz(w), z = __builtin_ctz(w);
-                            *lo++ = (uint16_t)(last - 31u + (uint32_t)a);
-                            *hi-- = (uint16_t)(last - (uint32_t)z);
-                            w &= 0x7FFFFFFFu >> a;
-                            w &= w - 1u;
+                        for (int e = 0; e < 4; ++e) {
+                            const float v = c[k][e];
+                            word[k] = __builtin_amdgcn_alignbit(word[k], __builtin_bit_cast(uint32_t, v), 31);
+                        }
+                }
+                __syncthreads();   // every read of the operands is done: the lists take their place
+                if (!in_tile) continue;
+                int own = 0;
+#pragma unroll
+                for (int k = 0; k < kWords; ++k) own += __popc(word[k]);
+                const uint32_t top = 4 * blocks - 1;   // place 0's bit
+                // the four lanes of a target list their hits one lane after the other
+                const int own16 = __shfl_xor(own, 16, kWave);
+                const int two = own + own16, two32 = __shfl_xor(two, 32, kWave);
+                const int before = ((quarter & 1) ? own16 : 0) + ((quarter & 2) ? two32 : 0);
+                const int all = two + two32;
+                const int mine = __shfl(all, lane / kShare, kWave);   // of the target the lane evaluates
+                // rounds of up to kCap listed hits per target (one, unless the
+                // particles are far denser than a lattice)
+                const bool fits = !__ballot(all > kCap);
+                for (int done = 0; __ballot(all > done); done += kCap) {
+                    uint16_t *to = list + lf * kListPitch;
+                    int pos = before - done;
+#pragma unroll
+                    for (int k = 0; k < kWords; ++k) {
+                        // a bit b stands for the source in slot last - b
+                        const uint32_t last = (uint32_t)((4 * k + quarter) * kPitch) + top;
+                        uint32_t w = word[k];
+                        if (fits) {
+                            // a word's hits from both ends at once; the last of an
+                            // odd number is written twice, to the same place
+                            uint16_t *lo = to + pos, *hi = to + (pos += __popc(w)) - 1;
+                            while (w) {
+                                const int a = __builtin_clz(w), z = __builtin_ctz(w);
+                                *lo++ = (uint16_t)(last - 31u + (uint32_t)a);
+                                *hi-- = (uint16_t)(last - (uint32_t)z);
+                                w &= 0x7FFFFFFFu >> a;
+                                w &= w - 1u;
+                            }
+                        } else {
+                            while (w) {
+                                const int z = __builtin_ctz(w);
+                                w &= w - 1u;
+                                if ((uint32_t)pos < (uint32_t)kCap) to[pos] = (uint16_t)(last - (uint32_t)z);
+                                ++pos;
+                            }
+                        }
+                    }
+                    wave_lds_sync();   // the lists are written
+                    const int left = mine - done;
+                    const int cnt = left < 0 ? 0 : (left < kCap ? left : kCap);
+                    const int most = wave_max_u7(cnt);
+                    // four lanes take a target's hits in turn (what a lane reads
+                    // past the list's end is not evaluated)
+                    const uint16_t *hits = list + le * kListPitch;
+                    auto slot = [&](int s) { return min((uint32_t)hits[s], (uint32_t)(kRows * kPitch - 1)); };
+                    if constexpr (W::kTwoAhead) {
+                        // while a pair is evaluated the next hit's record is read,
+                        // and the slot of the one after it
+                        real qa[kRec], qb[kRec];
+                        uint32_t ka = slot(sub), kb = slot(sub + kShare);
+                        fetch(ka, qa);
+                        ka = slot(sub + 2 * kShare);
+                        fetch(kb, qb);
+                        kb = slot(sub + 3 * kShare);
+                        for (int s = sub; s - sub < most; s += 2 * kShare) {
+                            if (s < cnt) eval(qa);
+                            fetch(ka, qa);
+                            ka = slot(s + 4 * kShare);
+                            if (s + kShare < cnt) eval(qb);
+                            fetch(kb, qb);
+                            kb = slot(s + 5 * kShare);
                         }
                     } else {
-                        while (w) {
-                            const int z = __builtin_ctz(w);
-                            w &= w - 1u;
-                            if ((uint32_t)pos < (uint32_t)kCap) to[pos] = (uint16_t)(last - (uint32_t)z);
-                            ++pos;
+                        real q[kRec];
+                        uint32_t k = slot(sub);   // the slot of the next hit is read ahead
+#pragma unroll 2
+                        for (int s = sub; s - sub < most; s += kShare) {
+                            fetch(k, q);
+                            k = slot(s + kShare);
+                            if (s < cnt) eval(q);
                         }
                     }
+                    wave_lds_sync();   // the lists are read
                 }
-                wave_lds_sync();   // the lists are written
-                const int left = mine - done;
-                const int cnt = left < 0 ? 0 : (left < kCap ? left : kCap);
-                const int most = wave_max_u7(cnt);
-                const uint16_t *hits = list[wave][lane / kShare];
-                // four lanes take a target's hits in turn (past the lane's last
-                // hit, that one is read again and not evaluated)
-                const int end = cnt > 0 ? cnt - 1 : 0;
-                if (cnt == 0) list[wave][lane / kShare][0] = 0;
-                auto slot = [&](int s) { return (uint32_t)hits[s < end ? s : end]; };
-                if constexpr (W::kTwoAhead) {
-                    // while a pair is evaluated the next hit's record is read,
-                    // and the slot of the one after it
-                    real qa[kRec], qb[kRec];
-                    uint32_t ka = slot(sub), kb = slot(sub + kShare);
-                    fetch(ka, qa);
-                    ka = slot(sub + 2 * kShare);
-                    fetch(kb, qb);
-                    kb = slot(sub + 3 * kShare);
-                    for (int s = sub; s - sub < most; s += 2 * kShare) {
-                        if (s < cnt) eval(qa);
-                        fetch(ka, qa);
-                        ka = slot(s + 4 * kShare);
-                        if (s + kShare < cnt) eval(qb);
-                        fetch(kb, qb);
-                        kb = slot(s + 5 * kShare);
-                    }
-                } else {
-                    real q[kRec];
-#pragma unroll 2
-                    for (int s = sub; s - sub < most; s += kShare) {
-                        fetch(slot(s), q);
-                        if (s < cnt) eval(q);
-                    }
-                }
-                wave_lds_sync();   // the lists are read
             }
         }
     }
@@ -897,8 +1035,9 @@ hipError_t go(const Params &P, const Grid &g, const sph_particles &tg, const uin
         const hipError_t e = hipEventRecord(ev_begin, s);
         if (e != hipSuccess) return e;
     }
+    const PairArgs<real> A{make_pair_k<real>(P), (real)P.R2, (float)(2.0 * P.h)};
     k_pairs<real, PASS, SOLID><<<div_up(tg.n, kGroup), kPairBlock, 0, s>>>(
-        P, g, view<real>(tg), tidx, nt, view<real>(sr), sstart, zero_first, view<real>(r),
+        A, g, view<real>(tg), tidx, nt, view<real>(sr), sstart, zero_first, view<real>(r),
         view<real>(rsrc ? *rsrc : none), view<real>(bar), cz);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return le;

@@ -82,7 +82,7 @@ struct PairK {
 };
 
 template <typename real>
-__device__ inline PairK<real> make_pair_k(const Params &P)
+inline PairK<real> make_pair_k(const Params &P)
 {
     PairK<real> K;
     K.hinv = (real)P.hinv;
