@@ -25,48 +25,54 @@ import torch
 
 from . import _lib as L
 from .sim import Sim
-from .state import Particles, Rates, cells_struct, real_dtype, stream_handle
+from .state import Particles, Rates, _Flat, cells_struct, real_dtype, stream_handle
 
 
-class Cotangent:
+class Cotangent(_Flat):
     """Device buffers of a state cotangent (sph_adjoint), in the form's
-    precision; with solid=True also of the deviatoric stress and the plastic
-    strain."""
+    precision, zero at first; with solid=True also of the deviatoric stress
+    and the plastic strain."""
 
     def __init__(self, n: int, prec: int, device, solid: bool = False):
         real = real_dtype(prec)
-        self.x = torch.zeros((3, n), dtype=real, device=device)
-        self.v = torch.zeros((3, n), dtype=real, device=device)
-        self.m, self.w, self.E, self.rho, self.p, self.c, self.e = [
-            torch.zeros(n, dtype=real, device=device) for _ in range(7)]
-        self.S = torch.zeros((6, n), dtype=real, device=device) if solid else None
-        self.ep = torch.zeros(n, dtype=real, device=device) if solid else None
+        self.n = n
+        self._allocate([("x", (3, n), real), ("v", (3, n), real)]
+                       + [(f, (n,), real) for f in ("m", "w", "E", "rho", "p", "c", "e")]
+                       + [("S", (6, n) if solid else None, real), ("ep", (n,) if solid else None, real)], device)
 
-    def _solid_fields(self, a):
-        if self.S is not None:
-            for k in range(6):
-                a.S[k] = self.S[k].data_ptr()
-            a.eps_p = self.ep.data_ptr()
+    def _bind(self):
+        super()._bind()
+        self._state = None
+
+    def _make_struct(self, scalars) -> L.SphAdjoint:
+        a = L.SphAdjoint()
+        if self.n == 0:
+            return a
+        for name in ("x", "v", "S"):
+            to = getattr(a, name)
+            for k, ptr in enumerate(self._addresses(name)):
+                to[k] = ptr
+        base = self._buf.data_ptr()
+        for name, field in scalars:
+            at = self._fields[field]
+            if at is not None:
+                setattr(a, name, base + at[0])
+        return a
+
+    STATE = (("m", "m"), ("omega", "w"), ("E", "E"), ("eps_p", "ep"))
+    DERIVED = (("rho", "rho"), ("p", "p"), ("c", "c"), ("e", "e"))
 
     def struct(self) -> L.SphAdjoint:
-        a = L.SphAdjoint()
-        for d in range(3):
-            a.x[d] = self.x[d].data_ptr()
-            a.v[d] = self.v[d].data_ptr()
-        a.m, a.omega, a.E = self.m.data_ptr(), self.w.data_ptr(), self.E.data_ptr()
-        a.rho, a.p, a.c, a.e = self.rho.data_ptr(), self.p.data_ptr(), self.c.data_ptr(), self.e.data_ptr()
-        self._solid_fields(a)
-        return a
+        """The ABI struct of these buffers (built once: they never move)."""
+        if self._struct is None:
+            self._struct = self._make_struct(self.STATE + self.DERIVED)
+        return self._struct
 
     def state_struct(self) -> L.SphAdjoint:
         """Only the state fields (what a permutation carries)."""
-        a = L.SphAdjoint()
-        for d in range(3):
-            a.x[d] = self.x[d].data_ptr()
-            a.v[d] = self.v[d].data_ptr()
-        a.m, a.omega, a.E = self.m.data_ptr(), self.w.data_ptr(), self.E.data_ptr()
-        self._solid_fields(a)
-        return a
+        if self._state is None:
+            self._state = self._make_struct(self.STATE)
+        return self._state
 
 
 class KineticEnergyRollout:
