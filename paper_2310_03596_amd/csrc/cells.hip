@@ -35,20 +35,24 @@ __device__ inline uint32_t bucket_of(const Grid &g, double x, double y, double z
 // of wavefronts).  Also clears the count of long empty-bucket runs that the
 // bucket table queues for the reorder.
 constexpr int kHashBlock = 1024;
-template <int D>
-__global__ __launch_bounds__(kHashBlock) void k_hash_hist(Grid g, uint32_t n, const double *__restrict__ x0,
-                                                          const double *__restrict__ x1,
-                                                          const double *__restrict__ x2,
-                                                          uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
-                                                          uint32_t *__restrict__ hist, uint32_t tiles,
-                                                          uint32_t *__restrict__ ngaps)
+template <int D, int ITEMS>
+constexpr int hash_threads = kBlock * ITEMS < kHashBlock ? kBlock * ITEMS : kHashBlock;
+template <int D, int ITEMS>
+__global__ __launch_bounds__((hash_threads<D, ITEMS>)) void k_hash_hist(Grid g, uint32_t n, const double *__restrict__ x0,
+                                                                        const double *__restrict__ x1,
+                                                                        const double *__restrict__ x2,
+                                                                        uint32_t *__restrict__ keys,
+                                                                        uint32_t *__restrict__ vals,
+                                                                        uint32_t *__restrict__ hist, uint32_t tiles,
+                                                                        bool by_tile, uint32_t *__restrict__ ngaps)
 {
+    constexpr int NT = hash_threads<D, ITEMS>;
     constexpr int BINS = 1 << D;
-    constexpr int TILE = kBlock * sort_items<D>;
-    static_assert(TILE % kHashBlock == 0, "a tile is whole rounds of the workgroup");
-    constexpr int IT = TILE / kHashBlock;
+    constexpr int TILE = kBlock * ITEMS;
+    static_assert(TILE % NT == 0, "a tile is whole rounds of the workgroup");
+    constexpr int IT = TILE / NT;
     __shared__ uint32_t h[BINS];
-    for (int b = threadIdx.x; b < BINS; b += kHashBlock) h[b] = 0;
+    for (int b = threadIdx.x; b < BINS; b += NT) h[b] = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) *ngaps = 0u;
     __syncthreads();
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -56,7 +60,7 @@ __global__ __launch_bounds__(kHashBlock) void k_hash_hist(Grid g, uint32_t n, co
     double p[IT][3];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const uint32_t e = base + it * kHashBlock + threadIdx.x;
+        const uint32_t e = base + it * NT + threadIdx.x;
         const bool valid = e < n;
         p[it][0] = valid ? x0[e] : 0.0;
         p[it][1] = valid ? x1[e] : 0.0;
@@ -64,7 +68,7 @@ __global__ __launch_bounds__(kHashBlock) void k_hash_hist(Grid g, uint32_t n, co
     }
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const uint32_t e = base + it * kHashBlock + threadIdx.x;
+        const uint32_t e = base + it * NT + threadIdx.x;
         const bool valid = e < n;
         const uint32_t key = bucket_of(g, p[it][0], p[it][1], p[it][2]);
         if (valid) {
@@ -74,7 +78,7 @@ __global__ __launch_bounds__(kHashBlock) void k_hash_hist(Grid g, uint32_t n, co
         hist_chunk<D>(h, valid ? key & (BINS - 1) : (uint32_t)BINS, valid);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < BINS; b += kHashBlock) hist[(size_t)b * tiles + tile] = h[b];
+    for (int b = threadIdx.x; b < BINS; b += NT) hist[hist_at<D>(b, tile, tiles, by_tile)] = h[b];
 }
 
 // Float offset from the bucket corner, ((x - o) - c L) evaluated in IEEE
@@ -85,17 +89,44 @@ __device__ inline float corner_offset(double x, double o, uint32_t c, double L)
     return (float)((x - o) - (double)c * L);
 }
 
+// Who writes the bucket table: the sort (its only pass has the scan of the
+// buckets), the reorder from the sorted keys, or a kernel of its own between
+// them, which leaves the long runs of empty buckets to the reorder.  A launch
+// costs 3 to 4 us, but a workgroup of the reorder fills alone the runs of empty
+// buckets that it meets, so it does so up to 65,536 buckets (256 rounds of
+// stores for a run of all of them).
+enum { kTableSorted, kTableHere, kTableListed };
+constexpr uint32_t kTableHereMost = 65536;
+constexpr uint32_t kShortRun = 8;   // buckets that one thread writes
+
 template <typename real>
 __global__ __launch_bounds__(kBlock) void k_gather(Grid g, PV<real> in, PV<real> out,
                                                    const uint32_t *__restrict__ keys,
                                                    const uint32_t *__restrict__ vals,
                                                    uint32_t *__restrict__ perm, int split,
-                                                   uint32_t *__restrict__ start,
+                                                   uint32_t *__restrict__ start, int table,
                                                    const uint32_t *__restrict__ ngaps,
                                                    const uint3 *__restrict__ gaps, uint32_t gap_cap)
 {
     uint32_t k = blockIdx.x * kBlock + threadIdx.x;
-    {
+    if (table == kTableHere) {
+        __shared__ uint3 q[kBlock];
+        __shared__ uint32_t nq;
+        if (threadIdx.x == 0) nq = 0;
+        __syncthreads();
+        if (k <= in.n) {
+            const uint32_t lo = k == 0 ? 0u : keys[k - 1] + 1u;
+            const uint32_t hi = k == in.n ? g.ncells : keys[k];   // buckets lo..hi start at k
+            if (lo <= hi && hi - lo < kShortRun) {
+                for (uint32_t c = lo; c <= hi; ++c) start[c] = k;
+            } else if (lo <= hi) {
+                q[atomicAdd(&nq, 1u)] = make_uint3(lo, hi, k);
+            }
+        }
+        __syncthreads();
+        for (uint32_t r = 0; r < nq; ++r)
+            for (uint32_t c = q[r].x + threadIdx.x; c <= q[r].y; c += kBlock) start[c] = q[r].z;
+    } else if (table == kTableListed) {
         // the bucket table's long runs of empty buckets, each spread over
         // every thread of the grid
         uint32_t m = *ngaps;
@@ -168,7 +199,6 @@ __global__ __launch_bounds__(kBlock) void k_gather(Grid g, PV<real> in, PV<real>
 // list that the reorder kernel, launched next, fills with all its threads;
 // if the list is full the workgroup fills the run.  Every start[c] is
 // written exactly once, and no thread walks a long run alone.
-constexpr uint32_t kShortRun = 8;
 constexpr uint32_t kLongRun = 16 * kBlock;
 constexpr int kStartItems = 2;
 __global__ __launch_bounds__(kBlock) void k_cell_start(const uint32_t *__restrict__ keys, uint32_t n,
@@ -365,36 +395,48 @@ hipError_t launch_build_cells(const Grid &g, int prec, const sph_particles &in, 
                               uint32_t *perm, uint32_t *start, const Workspace &ws, hipStream_t s)
 {
     uint32_t n = in.n;
-    uint32_t blocks = div_up(n, kBlock);
     if (n > 0) {
         // the list of long empty-bucket runs takes the histogram area once the
         // sort is done; its count sits in the first entry of counts
         uint32_t *ngaps = ws.counts;
         uint3 *gaps = reinterpret_cast<uint3 *>(ws.hist);
         const uint32_t gap_cap = (uint32_t)(((uint64_t)kMaxRadixBins * div_up(n, kSortTile)) / 3u);
-        const int D = radix_digit_bits(g.ncells);
-        if (D == 8)
-            k_hash_hist<8><<<sort_tiles<8>(n), kHashBlock, 0, s>>>(g, n, in.x[0], in.x[1], in.x[2], ws.keys[0],
-                                                               ws.vals[0], ws.hist, sort_tiles<8>(n), ngaps);
-        else if (D == 9)
-            k_hash_hist<9><<<sort_tiles<9>(n), kHashBlock, 0, s>>>(g, n, in.x[0], in.x[1], in.x[2], ws.keys[0],
-                                                               ws.vals[0], ws.hist, sort_tiles<9>(n), ngaps);
+        const SortPlan p = sort_plan(n, g.ncells);
+        auto hash = [&](auto kernel, int threads) {
+            kernel<<<p.tiles, threads, 0, s>>>(g, n, in.x[0], in.x[1], in.x[2], ws.keys[0], ws.vals[0], ws.hist, p.tiles,
+                                               p.by_tile, ngaps);
+        };
+        if (p.D == 8 && p.items == few_items<8>)
+            hash(k_hash_hist<8, few_items<8>>, hash_threads<8, few_items<8>>);
+        else if (p.D == 8)
+            hash(k_hash_hist<8, sort_items<8>>, hash_threads<8, sort_items<8>>);
+        else if (p.D == 9 && p.items == few_items<9>)
+            hash(k_hash_hist<9, few_items<9>>, hash_threads<9, few_items<9>>);
+        else if (p.D == 9)
+            hash(k_hash_hist<9, sort_items<9>>, hash_threads<9, sort_items<9>>);
+        else if (p.items == few_items<10>)
+            hash(k_hash_hist<10, few_items<10>>, hash_threads<10, few_items<10>>);
         else
-            k_hash_hist<10><<<sort_tiles<10>(n), kHashBlock, 0, s>>>(g, n, in.x[0], in.x[1], in.x[2], ws.keys[0],
-                                                                 ws.vals[0], ws.hist, sort_tiles<10>(n), ngaps);
-        const int cur = radix_sort(ws, n, g.ncells, s, true);
-        // the reorder also fills the long empty runs: enough threads that each
-        // takes at most 16 buckets of the longest, whatever n
-        const uint64_t gblocks64 = div_up((uint64_t)g.ncells + 1, (uint64_t)kBlock * 16u);
-        const uint32_t gblocks = blocks > gblocks64 ? blocks : (uint32_t)gblocks64;
-        k_cell_start<<<div_up((uint64_t)n + 1, (uint64_t)kBlock * kStartItems), kBlock, 0, s>>>(
-            ws.keys[cur], n, g.ncells, start, ngaps, gaps, gap_cap);
+            hash(k_hash_hist<10, sort_items<10>>, hash_threads<10, sort_items<10>>);
+        const int cur = radix_sort(ws, n, g.ncells, s, true, start);
+        const int table = p.passes == 1 ? kTableSorted : g.ncells <= kTableHereMost ? kTableHere : kTableListed;
+        uint64_t gblocks = div_up((uint64_t)n + (table == kTableHere ? 1 : 0), (uint64_t)kBlock);
+        if (table == kTableListed) {
+            // the reorder also fills the long empty runs: enough threads that each
+            // takes at most 16 buckets of the longest, whatever n
+            const uint64_t most = div_up((uint64_t)g.ncells + 1, (uint64_t)kBlock * 16u);
+            gblocks = gblocks > most ? gblocks : most;
+            k_cell_start<<<div_up((uint64_t)n + 1, (uint64_t)kBlock * kStartItems), kBlock, 0, s>>>(
+                ws.keys[cur], n, g.ncells, start, ngaps, gaps, gap_cap);
+        }
         if (prec == SPH_FP64)
-            k_gather<double><<<gblocks, kBlock, 0, s>>>(g, view<double>(in), view<double>(out), ws.keys[cur],
-                                                        ws.vals[cur], perm, 0, start, ngaps, gaps, gap_cap);
+            k_gather<double><<<(uint32_t)gblocks, kBlock, 0, s>>>(g, view<double>(in), view<double>(out), ws.keys[cur],
+                                                                  ws.vals[cur], perm, 0, start, table, ngaps, gaps,
+                                                                  gap_cap);
         else
-            k_gather<float><<<gblocks, kBlock, 0, s>>>(g, view<float>(in), view<float>(out), ws.keys[cur],
-                                                       ws.vals[cur], perm, 1, start, ngaps, gaps, gap_cap);
+            k_gather<float><<<(uint32_t)gblocks, kBlock, 0, s>>>(g, view<float>(in), view<float>(out), ws.keys[cur],
+                                                                 ws.vals[cur], perm, 1, start, table, ngaps, gaps,
+                                                                 gap_cap);
     } else {
         k_start_empty<<<div_up((uint64_t)g.ncells + 1, kBlock), kBlock, 0, s>>>(g.ncells, start);
     }

@@ -2,7 +2,7 @@
 // workspace, with digits of 8 to 10 bits chosen so that a key takes as few
 // passes as possible (two for keys of up to 20 bits).  Each pass: (1)
 // per-tile digit histograms in LDS, (2) one workgroup per digit scans that
-// digit's counts over tiles, (3) each tile ranks its keys stably with
+// digit's counts over tiles (not in small sorts), (3) each tile ranks its keys stably with
 // wavefront ballots (one ballot per digit bit gives every lane the mask of
 // lanes holding the same digit; popcount of the lanes below gives the rank
 // inside the wavefront) and scatters.  Used for the bucket sort (Section I)
@@ -34,6 +34,14 @@ __device__ inline uint32_t wave_incl_scan(uint32_t v)
         if (lane >= off) v += t;
     }
     return v;
+}
+
+// Orders this wavefront's LDS accesses before its following ones.
+__device__ inline void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Exclusive scan over the NT threads of a block; every thread gets `total`.
@@ -127,15 +135,23 @@ __device__ inline void hist_chunk(uint32_t *h, uint32_t d, bool valid)
     if (valid && head) atomicAdd(&h[d], (uint32_t)(next - lane));
 }
 
+// A tile's digit counts lie in one run per tile where the scatter adds up the
+// tiles' counts itself (few tiles), and digit by digit where a kernel scans
+// each digit's counts over the tiles first.
 template <int D>
+__device__ inline size_t hist_at(uint32_t digit, uint32_t tile, uint32_t tiles, bool by_tile)
+{
+    return by_tile ? (size_t)tile * (1u << D) + digit : (size_t)digit * tiles + tile;
+}
+
+template <int D, int IT>
 __global__ __launch_bounds__(kBlock) void k_upsweep(const uint32_t *__restrict__ keys, uint32_t n, int shift,
-                                                    uint32_t *__restrict__ hist, uint32_t tiles)
+                                                    uint32_t *__restrict__ hist, uint32_t tiles, bool by_tile)
 {
     constexpr int BINS = 1 << D;
     __shared__ uint32_t h[BINS];
     for (int b = threadIdx.x; b < BINS; b += kBlock) h[b] = 0;
     __syncthreads();
-    constexpr int IT = sort_items<D>;
     // Consecutive tiles run on one XCD: a digit's counts of 32 consecutive
     // tiles share one 128-byte line of hist, which is then written (here)
     // and read (in the scatter) through a single L2 instead of eight.
@@ -154,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void k_upsweep(const uint32_t *__restrict__
         hist_chunk<D>(h, valid ? (keyv[it] >> shift) & (BINS - 1) : (uint32_t)BINS, valid);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < BINS; b += kBlock) hist[(size_t)b * tiles + tile] = h[b];
+    for (int b = threadIdx.x; b < BINS; b += kBlock) hist[hist_at<D>(b, tile, tiles, by_tile)] = h[b];
 }
 
 // One workgroup per digit: exclusive scan of that digit's tile counts.
@@ -165,66 +181,99 @@ __global__ __launch_bounds__(kBlock) void k_scan_digit(uint32_t *__restrict__ hi
     if (threadIdx.x == 0) totals[blockIdx.x] = tot;
 }
 
-template <int D>
+// Scatter of one pass.  Each wavefront takes IT * 64 consecutive keys of the
+// tile and counts its digits as it ranks them, without a barrier; the four
+// counts of a digit then become its wavefronts' first places, and the keys
+// are written.  (With a round of the whole workgroup and three barriers for
+// every 256 keys: 8,000 keys of 9 bits 7.2 us, of 10 bits 13.1, the 810,448 of
+// the column 11.0, 4 M of 10 bits 32; now 4.6, 5.3, 8.3 and 23.)
+// Where the whole key is one digit, the scan of the digits is the bucket
+// table: with `start`, the first tile writes it (buckets 0 .. nkeys).
+template <int D, int IT>
 __global__ __launch_bounds__(kBlock) void k_downsweep(const uint32_t *__restrict__ kin,
                                                       const uint32_t *__restrict__ vin,
                                                       uint32_t *__restrict__ kout,
                                                       uint32_t *__restrict__ vout, uint32_t n, int shift,
                                                       const uint32_t *__restrict__ hist, uint32_t tiles,
-                                                      const uint32_t *__restrict__ totals)
+                                                      const uint32_t *__restrict__ totals, bool by_tile,
+                                                      uint32_t *__restrict__ start, uint32_t nkeys)
 {
     constexpr int BINS = 1 << D;
     constexpr int PT = BINS / kBlock;   // digits per thread in the bookkeeping
     static_assert(BINS % kBlock == 0, "digits must cover the block");
     constexpr int NW = kBlock / kWave;
-    __shared__ uint32_t dbase[BINS];
-    __shared__ uint32_t run[BINS];
     __shared__ uint32_t cnt[NW][BINS];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     // the tile's keys and values are read first: their loads overlap the
-    // digit-base bookkeeping below and each other (a load issued inside the
-    // loop would wait out a full round trip behind every barrier)
-    constexpr int IT = sort_items<D>;
-    // the tile order of the histogram pass (same XCD for consecutive tiles,
-    // so the runs they write side by side in each digit's range fill whole
-    // lines in one L2)
+    // digit-base bookkeeping below and each other.  The tile order is that of
+    // the histogram pass (same XCD for consecutive tiles, so the runs they
+    // write side by side in each digit's range fill whole lines in one L2).
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const uint32_t base = tile * (kBlock * IT);
+    const uint32_t base = tile * (kBlock * IT) + (uint32_t)(wave * (IT * kWave) + lane);
     uint32_t keyv[IT], valv[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const uint32_t e = base + it * kBlock + tid;
+        const uint32_t e = base + it * kWave;
         keyv[it] = e < n ? kin[e] : 0u;
         valv[it] = e < n ? vin[e] : 0u;
     }
+#pragma unroll
+    for (int k = 0; k < BINS / kWave; ++k) cnt[wave][k * kWave + lane] = 0;
     // digit bases of this tile: exclusive scan of the digit totals (each
     // thread holds PT consecutive digits) plus the tile's offset in its digit
-    uint32_t loc[PT];
+    uint32_t first[PT], mine[PT];
     uint32_t sum = 0;
+    if (by_tile) {
+        uint32_t all[PT];
 #pragma unroll
-    for (int k = 0; k < PT; ++k) {
-        loc[k] = sum;
-        sum += totals[tid * PT + k];
+        for (int k = 0; k < PT; ++k) all[k] = mine[k] = 0;
+        const uint32_t *h = hist + tid * PT;
+        constexpr uint32_t U = 32 / PT;   // tiles whose counts are in flight
+        for (uint32_t t0 = 0; t0 < tiles; t0 += U) {
+            uint32_t c[U][PT];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t t = t0 + u < tiles ? t0 + u : tiles - 1u;
+#pragma unroll
+                for (int k = 0; k < PT; ++k) c[u][k] = h[(size_t)t * BINS + k];
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+#pragma unroll
+                for (int k = 0; k < PT; ++k) {
+                    all[k] += t0 + u < tiles ? c[u][k] : 0u;
+                    mine[k] += t0 + u < tile ? c[u][k] : 0u;
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            first[k] = sum;
+            sum += all[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            first[k] = sum;
+            sum += totals[tid * PT + k];
+            mine[k] = hist[(size_t)(tid * PT + k) * tiles + tile];
+        }
     }
     uint32_t tot;
     const uint32_t ex = block_excl_scan(sum, tot);
 #pragma unroll
     for (int k = 0; k < PT; ++k) {
-        const int d = tid * PT + k;
-        dbase[d] = ex + loc[k] + hist[(size_t)d * tiles + tile];
-        run[d] = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) cnt[w][d] = 0;
+        const uint32_t d = (uint32_t)(tid * PT + k);
+        first[k] += ex;
+        if (start && tile == 0 && d <= nkeys) start[d] = first[k];
+        if (start && tile == 0 && d + 1 == BINS && nkeys == BINS) start[BINS] = n;
     }
-    __syncthreads();
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t rankv[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const uint32_t e = base + it * kBlock + tid;
-        const bool valid = e < n;
-        const uint32_t key = keyv[it];
-        const uint32_t val = valv[it];
-        uint32_t d = (key >> shift) & (BINS - 1);
+        const bool valid = base + it * kWave < n;
+        const uint32_t d = (keyv[it] >> shift) & (BINS - 1);
         // Rank among the lanes of this wavefront with the same digit.  When the
         // valid lanes' digits do not decrease (the usual case: the keys arrive
         // nearly sorted), each digit is one run of lanes and the rank is the
@@ -238,11 +287,11 @@ __global__ __launch_bounds__(kBlock) void k_downsweep(const uint32_t *__restrict
             const bool head = valid && (lane == 0 || d != prev);
             const uint64_t heads = __ballot(head) | ~vmask;   // invalid lanes end the last run
             const uint64_t upto = heads & (lane == kWave - 1 ? ~0ull : ((2ull << lane) - 1ull));
-            const int start = 63 - __clzll((long long)upto);
+            const int from = 63 - __clzll((long long)upto);
             const uint64_t above = heads & ~(lane == kWave - 1 ? ~0ull : ((2ull << lane) - 1ull));
             const int next = above ? __ffsll((unsigned long long)above) - 1 : kWave;
-            rank = (uint32_t)(lane - start);
-            count = (uint32_t)(next - start);
+            rank = (uint32_t)(lane - from);
+            count = (uint32_t)(next - from);
             leader = valid && next == lane + 1;
         } else {
             uint64_t mask = vmask;
@@ -256,49 +305,82 @@ __global__ __launch_bounds__(kBlock) void k_downsweep(const uint32_t *__restrict
             count = (uint32_t)__popcll(mask);
             leader = valid && ((mask >> lane) == 1ull);
         }
-        if (leader) cnt[wave][d] = count;
-        __syncthreads();
-        if (valid) {
-            uint32_t pre = run[d];
-            for (int w = 0; w < wave; ++w) pre += cnt[w][d];
-            uint32_t pos = dbase[d] + pre + rank;
-            kout[pos] = key;
-            vout[pos] = val;
-        }
-        __syncthreads();
+        const uint32_t seen = valid ? cnt[wave][d] : 0u;   // by this wavefront, so far
+        wave_lds_order();
+        if (leader) cnt[wave][d] = seen + count;
+        wave_lds_order();
+        rankv[it] = seen + rank;
+    }
+    __syncthreads();
 #pragma unroll
-        for (int k = 0; k < PT; ++k) {
-            const int b = tid * PT + k;
-            uint32_t add = 0;
+    for (int k = 0; k < PT; ++k) {
+        uint32_t at = first[k] + mine[k];
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                add += cnt[w][b];
-                cnt[w][b] = 0;
-            }
-            run[b] += add;
+        for (int w = 0; w < NW; ++w) {
+            const uint32_t c = cnt[w][tid * PT + k];
+            cnt[w][tid * PT + k] = at;
+            at += c;
         }
-        __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        if (base + it * kWave < n) {
+            const uint32_t pos = cnt[wave][(keyv[it] >> shift) & (BINS - 1)] + rankv[it];
+            kout[pos] = keyv[it];
+            vout[pos] = valv[it];
+        }
     }
 }
 
-// Keys per tile and tiles of a pass with D-bit digits over n keys.
+// How a sort of n keys below nkeys goes: digits of D bits, in tiles of
+// kBlock * items keys.  While a tile's workgroup can read every tile's counts
+// (64 KB at most) the scatter adds them up itself, 32 loads in flight, and the
+// scan's launch (3.6 to 4.6 us a pass) is saved: up to 131,072 keys of 8-bit
+// digits, 65,536 of wider ones (there a 100,000-key pass takes 7.1 us, and 7.2
+// with a scan beside it; beyond, the counts read grow with the square of n).
+// Up to 32,768 keys the tiles are also a quarter or half as long, so that more
+// workgroups share the work (the workspace holds n / 2 counts).
+struct SortPlan {
+    int D, passes, items;
+    uint32_t tiles;
+    bool by_tile;
+};
+
+inline int key_bits(uint32_t nkeys);
+inline int radix_digit_bits(uint32_t nkeys);
 template <int D>
-inline uint32_t sort_tiles(uint32_t n)
+constexpr int few_items = 1 << (D - 7);   // 2, 4, 8
+
+inline SortPlan sort_plan(uint32_t n, uint32_t nkeys)
 {
-    return div_up(n, (uint64_t)kBlock * sort_items<D>);   // at most the workspace's tiles
+    SortPlan p;
+    const int bits = key_bits(nkeys);
+    p.passes = bits > 0 ? (bits + kMaxRadixBits - 1) / kMaxRadixBits : 1;
+    p.D = radix_digit_bits(nkeys);
+    const uint32_t most = 16384u >> p.D;   // tiles of 64 KB of counts
+    p.items = p.D == 8 ? few_items<8> : p.D == 9 ? few_items<9> : few_items<10>;
+    p.tiles = div_up(n, (uint64_t)kBlock * p.items);
+    if (p.tiles > most) {
+        p.items = p.D == 10 ? sort_items<10> : sort_items<9>;
+        p.tiles = div_up(n, (uint64_t)kBlock * p.items);
+    }
+    p.by_tile = p.tiles <= most;
+    return p;
 }
 
 // One LSD pass with D-bit digits starting at bit `shift`; with hist_ready the
 // per-tile digit counts are already in ws.hist (written by the kernel that
-// produced the keys, over the same tiles).
-template <int D>
-void sort_pass(const Workspace &ws, uint32_t n, int shift, int cur, hipStream_t s, bool hist_ready = false)
+// produced the keys, over the same tiles).  With `start`, also the bucket
+// table of a sort of one pass.
+template <int D, int IT>
+void sort_pass(const Workspace &ws, const SortPlan &p, uint32_t n, int shift, int cur, hipStream_t s,
+               bool hist_ready, uint32_t *start, uint32_t nkeys)
 {
-    const uint32_t tiles = sort_tiles<D>(n);
-    if (!hist_ready) k_upsweep<D><<<tiles, kBlock, 0, s>>>(ws.keys[cur], n, shift, ws.hist, tiles);
-    k_scan_digit<<<1u << D, kBlock, 0, s>>>(ws.hist, tiles, ws.totals);
-    k_downsweep<D><<<tiles, kBlock, 0, s>>>(ws.keys[cur], ws.vals[cur], ws.keys[cur ^ 1], ws.vals[cur ^ 1], n,
-                                            shift, ws.hist, tiles, ws.totals);
+    if (!hist_ready) k_upsweep<D, IT><<<p.tiles, kBlock, 0, s>>>(ws.keys[cur], n, shift, ws.hist, p.tiles, p.by_tile);
+    if (!p.by_tile) k_scan_digit<<<1u << D, kBlock, 0, s>>>(ws.hist, p.tiles, ws.totals);
+    k_downsweep<D, IT><<<p.tiles, kBlock, 0, s>>>(ws.keys[cur], ws.vals[cur], ws.keys[cur ^ 1], ws.vals[cur ^ 1], n,
+                                                  shift, ws.hist, p.tiles, ws.totals, p.by_tile, start, nkeys);
 }
 
 // Number of bits needed for keys below nkeys.
@@ -322,21 +404,28 @@ inline int radix_digit_bits(uint32_t nkeys)
 // Sorts (ws.keys[0], ws.vals[0]) of n entries, keys below nkeys; returns the
 // index of the key/value buffer pair that holds the result.  With
 // first_hist, the first pass's per-tile digit counts are already in ws.hist.
-inline int radix_sort(const Workspace &ws, uint32_t n, uint32_t nkeys, hipStream_t s, bool first_hist = false)
+// A sort of one pass also writes the bucket table to `start`, if given.
+inline int radix_sort(const Workspace &ws, uint32_t n, uint32_t nkeys, hipStream_t s, bool first_hist = false,
+                      uint32_t *start = nullptr)
 {
-    const int bits = key_bits(nkeys);
-    const int passes = bits > 0 ? (bits + kMaxRadixBits - 1) / kMaxRadixBits : 1;
-    const int dbits = radix_digit_bits(nkeys);
+    const SortPlan p = sort_plan(n, nkeys);
+    if (p.passes > 1) start = nullptr;
     int cur = 0;
-    for (int ps = 0; ps < passes; ++ps) {
-        const int shift = ps * dbits;
+    for (int ps = 0; ps < p.passes; ++ps) {
+        const int shift = ps * p.D;
         const bool ready = first_hist && ps == 0;
-        if (dbits == 8)
-            sort_pass<8>(ws, n, shift, cur, s, ready);
-        else if (dbits == 9)
-            sort_pass<9>(ws, n, shift, cur, s, ready);
+        if (p.D == 8 && p.items == few_items<8>)
+            sort_pass<8, few_items<8>>(ws, p, n, shift, cur, s, ready, start, nkeys);
+        else if (p.D == 8)
+            sort_pass<8, sort_items<8>>(ws, p, n, shift, cur, s, ready, start, nkeys);
+        else if (p.D == 9 && p.items == few_items<9>)
+            sort_pass<9, few_items<9>>(ws, p, n, shift, cur, s, ready, start, nkeys);
+        else if (p.D == 9)
+            sort_pass<9, sort_items<9>>(ws, p, n, shift, cur, s, ready, start, nkeys);
+        else if (p.items == few_items<10>)
+            sort_pass<10, few_items<10>>(ws, p, n, shift, cur, s, ready, start, nkeys);
         else
-            sort_pass<10>(ws, n, shift, cur, s, ready);
+            sort_pass<10, sort_items<10>>(ws, p, n, shift, cur, s, ready, start, nkeys);
         cur ^= 1;
     }
     return cur;
