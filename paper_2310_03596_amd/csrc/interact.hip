@@ -6,26 +6,26 @@
 // x-fastest), so each row is one contiguous range of the sorted sources.
 //
 // Work mapping (k_pairs): a workgroup of four wavefronts takes 64
-// consecutive targets, in groups that share a bucket row (cy, cz); consecutive
-// sorted targets almost always do.
+// consecutive targets (32 or 16 where the call is small), in groups that share
+// a bucket row (cy, cz); consecutive sorted targets almost always do.
 //   * The window of a group is the 9 neighbour rows over the union of its
 //     targets' buckets, about 800 sources on a lattice.  The workgroup first
 //     reads their positions and culls those that are farther than 2h from the
 //     box of its targets (435 remain of a lattice's, 600 of a disordered
 //     fluid's), then loads the others once, straight from the particle fields,
 //     and keeps the whole records in LDS (in pages when they fill more than one).
-//   * Each wavefront takes 16 of the targets.  The candidate test of 16
+//   * Each wavefront takes 16 (8, 4) of the targets.  The candidate test of 16
 //     sources against 16 targets is one matrix product (K = 4) on the matrix
 //     cores, with the test's bound as its initial value, so the sign of each
 //     result is the answer and one instruction per result collects the signs
 //     in a bit mask per lane.
-//   * The hits of a target go to its list in LDS, and four lanes share the
-//     list evenly: only ~1 candidate in 6 is a neighbour, so the cheap test
+//   * The hits of a target go to its list in LDS, and four (8, 16) lanes share
+//     the list evenly: only ~1 candidate in 6 is a neighbour, so the cheap test
 //     and the pair body (about a hundred operations) are kept apart, and the
 //     body runs dense.  (One lane per target would leave the chip idle below
 //     some 60,000 particles, and wait for its busiest lane.)
-// The four lanes' sums are added at the end.  The order of summation depends
-// on the particles' order alone, so repeated calls agree bit for bit.  A pair
+// The lanes' sums are added at the end.  The order of summation depends
+// on the particles' order and number alone, so repeated calls agree bit for bit.  A pair
 // with r = 0 (the target itself, or a coincident particle) adds nothing: its
 // terms all carry F(0) = 0.
 //
@@ -47,7 +47,7 @@
 // 4.0 M cylinder (FP32) FORCE 2.89, 2.59, 2.39 ms, GRADIENT 1.62, 1.50, 1.31;
 // 6.7 M impact (FP64) FORCE 8.83, 6.53, 6.15 ms, GRADIENT 4.02, 3.04, 2.80;
 // 250,047-particle FORCE reverse FP32 260, 248, 233 us; 27,000 ones FP64 FORCE
-// 54, 43, 39 us; 8,000 ones FP32 63, 33, 28 us.  Culling and loading in one
+// 54, 43, 39 us; 8,000 ones FP32 63, 33, 28 us (17 with 16 targets per workgroup).  Culling and loading in one
 // sweep instead of two was slower (441 us for the column's 373): each
 // source's fields then wait for its position.
 //
@@ -68,11 +68,9 @@ namespace {
 // Events recorded around every pair-kernel launch when set (sph_set_pair_events).
 std::atomic<void *> g_pair_events[2] = {nullptr, nullptr};
 
-constexpr int kTile = 16;                         // targets per wavefront
 constexpr int kPairWaves = 4;                     // wavefronts per workgroup
 constexpr int kPairBlock = kPairWaves * kWave;    // threads per workgroup
-constexpr int kGroup = kPairWaves * kTile;        // targets per workgroup (one per lane of a wavefront)
-constexpr int kShare = kWave / kTile;             // lanes that share a target
+constexpr uint32_t kCUs = 256;
 // Sources in flight per lane while the window is culled (column FP32: 1 364,
 // 2 362, 4 368 us).
 constexpr int kAhead = 2;
@@ -80,7 +78,6 @@ constexpr int kSeg = 384;                         // entries of a batch that a w
 constexpr int kBatch = kPairWaves * kSeg;         // window entries culled at a time (a lattice's windows: 800 to 1,450)
 constexpr int kEntryBits = 11;                    // of a kept entry's code: its place in the batch, then its row
 static_assert(kBatch <= 1 << kEntryBits && kSeg % (kWave * kAhead) == 0, "a batch's entries");
-static_assert(kGroup == kWave, "lane l of every wavefront looks at target l of the workgroup");
 constexpr int kPassAdjoint = 2;            // reverse mode of the FORCE pass
 constexpr int kPassGradAdjoint = 4;        // reverse mode of the GRADIENT pass
 constexpr int kPassCensus = 3;             // neighbour census of a FORCE or GRADIENT pass
@@ -110,8 +107,11 @@ __device__ inline unsigned long long mix64(uint32_t id)
 // (c_j - c_i) L of its row in y and z.  Held in planes of 16 bytes per source,
 // the last one of 8 bytes where that is enough, so that a hit costs a few wide
 // LDS reads.
-template <typename real, int PASS, bool SOLID>
+template <typename real, int PASS, bool SOLID, int TILE = 16>
 struct Pass {
+    static constexpr int kGroup = kPairWaves * TILE;   // targets per workgroup
+    static constexpr int kShare = kWave / TILE;        // lanes that share a target
+    static_assert(TILE <= 16 && kGroup <= kWave, "lane l of every wavefront looks at target l of the workgroup");
     static constexpr bool SPLIT = sizeof(real) == 4;
     static constexpr bool ADJ = PASS == kPassAdjoint, GADJ = PASS == kPassGradAdjoint, CENSUS = PASS == kPassCensus;
     static constexpr bool FORCE = PASS == SPH_PASS_FORCE, GRAD = PASS == SPH_PASS_GRADIENT;
@@ -153,7 +153,7 @@ struct Pass {
     // (pitch 4 or 12 modulo 16).
     static constexpr int kBudget = 128 / waves * 1280 - kBatch * 2 - 128;
     static constexpr int kListPitch = kCap + 2;   // (+ 2: the rows start in different banks)
-    static constexpr int kListBytes = kGroup * kListPitch * 2 + 64;
+    static constexpr int kListBytes = (kGroup * kListPitch + 6 * kShare) * 2;   // (a lane reads up to six ahead)
     static constexpr int most_of(int a, int b) { return a > b ? a : b; }
     static constexpr int REC = 16 * NV + (HALF ? 8 : 0);
     static constexpr int up4(int places) { return (places + 3) / 4 * 4; }
@@ -270,19 +270,24 @@ __device__ inline float unordered(uint32_t u)
     return __builtin_bit_cast(float, u ^ (~(uint32_t)((int)u >> 31) | 0x80000000u));
 }
 
-// The sum of v over the four lanes 4 k .. 4 k + 3, in each of them.
+// v of another lane of the row of 16, as the data-parallel move CTRL names it.
 template <int CTRL>
-__device__ inline double quad_other(double v)
+__device__ inline double lane_other(double v)
 {
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
-__device__ inline double quad_sum(double v)
+// The sum of v over the N lanes N k .. N k + N - 1, in each of them.
+template <int N>
+__device__ inline double share_sum(double v)
 {
-    v += quad_other<0xB1>(v);   // lanes 1 0 3 2
-    return v + quad_other<0x4E>(v);   // lanes 2 3 0 1
+    v += lane_other<0xB1>(v);   // lanes 1 0 3 2
+    v += lane_other<0x4E>(v);   // lanes 2 3 0 1
+    if constexpr (N > 4) v += lane_other<0x141>(v);   // lanes 7 .. 0 of 8: the other four
+    if constexpr (N > 8) v += lane_other<0x140>(v);   // lanes 15 .. 0 of 16: the other eight
+    return v;
 }
 
 // Target position: bucket offsets and bucket x index (split), or x (FP64).
@@ -367,16 +372,17 @@ struct PairArgs {
     float h2;   // 2h
 };
 
-template <typename real, int PASS, bool SOLID>
+template <typename real, int PASS, bool SOLID, int TILE>
 __global__ __launch_bounds__(kPairBlock)
 __attribute__((amdgpu_waves_per_eu(Pass<real, PASS, SOLID>::waves)))
 void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, const uint32_t *__restrict__ ntdev,
              PV<real> src, const uint32_t *__restrict__ sstart, int zero_first, RV<real> R, RV<real> Rsrc, AV<real> B,
              Census cz)
 {
-    using W = Pass<real, PASS, SOLID>;
+    using W = Pass<real, PASS, SOLID, TILE>;
     constexpr bool SPLIT = W::SPLIT, ADJ = W::ADJ, GADJ = W::GADJ, CENSUS = W::CENSUS, FORCE = W::FORCE;
     constexpr int NOUT = W::NOUT, kPage = W::kPage, kCap = W::kCap, C = W::C;
+    constexpr int kGroup = W::kGroup, kShare = W::kShare;
     constexpr int kRows = W::kRows, kPitch = W::kPitch, kCandPitch = W::kCandPitch;
     constexpr int kWords = kRows / 4;   // bit-mask words of a lane per page
     using full = typename Chunk<real>::full;
@@ -404,15 +410,16 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
     }
     // lane l of every wavefront looks at target l of the workgroup
     const uint32_t t = tile * (uint32_t)kGroup + (uint32_t)lane;
-    uint32_t ti = t < nt ? (tidx ? tidx[t] : t) : tg.n;
+    uint32_t ti = lane < kGroup && t < nt ? (tidx ? tidx[t] : t) : tg.n;
     const bool tvalid = ti < tg.n;   // a listed index outside the target array names no target
     ti = tvalid ? ti : 0u;
     const uint32_t th = tg.hash[ti];
     const uint32_t trow = th / (uint32_t)g.nx;   // cy + ny cz
     const int tcx = (int)(th - trow * (uint32_t)g.nx);
     // the lane's target in the candidate test, and the one whose pairs it evaluates
-    const int lf = wave * kTile + (lane & (kTile - 1)), le = wave * kTile + lane / kShare;
-    const int sub = lane & (kShare - 1), quarter = lane / kTile;
+    // (of a test's 16 columns, the first TILE hold targets)
+    const int lf = wave * TILE + (lane & (TILE - 1)), le = wave * TILE + lane / kShare;
+    const int sub = lane & (kShare - 1), quarter = lane / 16;
     const uint32_t i = __shfl(ti, le, kWave);
     const int ecx = __shfl(tcx, le, kWave);
     uint64_t pending = __ballot(tvalid);
@@ -563,8 +570,8 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
         pending &= ~in64;
         const int lcx = __builtin_amdgcn_readlane(tcx, leader);   // origin of the group's frame along x
         const int gz = (int)(key / (uint32_t)g.ny), gy = (int)(key - (uint32_t)gz * (uint32_t)g.ny);
-        const bool fin = (in64 >> lf) & 1ull;
-        const uint32_t in_tile = (uint32_t)(in64 >> (wave * kTile)) & 0xFFFFu;
+        const bool fin = (lane & 15) < TILE && (in64 >> lf) & 1ull;
+        const uint32_t in_tile = (uint32_t)(in64 >> (wave * TILE)) & ((1u << TILE) - 1u);
         T.cxf = (real)(ecx - lcx);
         // Frame of the candidate test, in FP32 in both forms: positions relative
         // to the corner of bucket (lcx, gy, gz); split form ((c - lcx) L + off)
@@ -829,7 +836,7 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
 #pragma unroll
                 for (int k = 0; k < kWords; ++k) own += __popc(word[k]);
                 const uint32_t top = 4 * blocks - 1;   // place 0's bit
-                // the four lanes of a target list their hits one lane after the other
+                // the four lanes that tested a target list its hits one after the other
                 const int own16 = __shfl_xor(own, 16, kWave);
                 const int two = own + own16, two32 = __shfl_xor(two, 32, kWave);
                 const int before = ((quarter & 1) ? own16 : 0) + ((quarter & 2) ? two32 : 0);
@@ -870,7 +877,7 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
                     const int left = mine - done;
                     const int cnt = left < 0 ? 0 : (left < kCap ? left : kCap);
                     const int most = wave_max_u7(cnt);
-                    // four lanes take a target's hits in turn (what a lane reads
+                    // a target's lanes take its hits in turn (what a lane reads
                     // past the list's end is not evaluated)
                     const uint16_t *hits = list + le * kListPitch;
                     auto slot = [&](int s) { return min((uint32_t)hits[s], (uint32_t)(kRows * kPitch - 1)); };
@@ -908,13 +915,14 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
     }
 
     if constexpr (CENSUS) {
-        ncen += __shfl_xor(ncen, 1, kWave);
-        ncen += __shfl_xor(ncen, 2, kWave);
-        scen += __shfl_xor(scen, 1, kWave);
-        scen += __shfl_xor(scen, 2, kWave);
+#pragma unroll
+        for (int off = 1; off < kShare; off <<= 1) {
+            ncen += __shfl_xor(ncen, off, kWave);
+            scen += __shfl_xor(scen, off, kWave);
+        }
     } else {
 #pragma unroll
-        for (int k = 0; k < NOUT; ++k) acc[k].s = quad_sum(acc[k].s);
+        for (int k = 0; k < NOUT; ++k) acc[k].s = share_sum<kShare>(acc[k].s);
     }
     if (!valid || sub != 0) return;
     if constexpr (CENSUS) {
@@ -1036,9 +1044,26 @@ hipError_t go(const Params &P, const Grid &g, const sph_particles &tg, const uin
         if (e != hipSuccess) return e;
     }
     const PairArgs<real> A{make_pair_k<real>(P), (real)P.R2, (float)(2.0 * P.h)};
-    k_pairs<real, PASS, SOLID><<<div_up(tg.n, kGroup), kPairBlock, 0, s>>>(
-        A, g, view<real>(tg), tidx, nt, view<real>(sr), sstart, zero_first, view<real>(r),
-        view<real>(rsrc ? *rsrc : none), view<real>(bar), cz);
+    auto launch = [&](auto kernel, int group) {
+        kernel<<<div_up(tg.n, group), kPairBlock, 0, s>>>(A, g, view<real>(tg), tidx, nt, view<real>(sr), sstart, zero_first,
+                                                          view<real>(r), view<real>(rsrc ? *rsrc : none), view<real>(bar),
+                                                          cz);
+    };
+    // The fewest targets per wavefront whose workgroups are all resident at
+    // once (one per SIMD's wavefront on each CU): below that a call is bound by
+    // the latency of one workgroup's chain of loads, barriers and bucket rows,
+    // which fewer targets shorten; above it their windows overlap more and the
+    // chip is full.  16, 8 and 4 targets, in us: FORCE FP32 of 1,728 particles
+    // 33, 19, 15; 8,000 28, 20, 17; 27,000 32, 28, 31; 46,656 37.5, 37.6, 45;
+    // 64,000 41, 47, 57; solid FP64 FORCE of 4,096 30, 22, 14; 13,824 33, 27,
+    // 30; its reverse (one workgroup per CU) 61, 38, 24 and 63, 65, 78.
+    constexpr uint32_t resident = kCUs * Pass<real, PASS, SOLID>::waves;
+    if (div_up(tg.n, Pass<real, PASS, SOLID, 4>::kGroup) <= resident)
+        launch(k_pairs<real, PASS, SOLID, 4>, Pass<real, PASS, SOLID, 4>::kGroup);
+    else if (div_up(tg.n, Pass<real, PASS, SOLID, 8>::kGroup) <= resident)
+        launch(k_pairs<real, PASS, SOLID, 8>, Pass<real, PASS, SOLID, 8>::kGroup);
+    else
+        launch(k_pairs<real, PASS, SOLID, 16>, Pass<real, PASS, SOLID, 16>::kGroup);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return le;
     if (ev_begin && ev_end) return hipEventRecord(ev_end, s);
