@@ -54,30 +54,47 @@ __device__ inline void eos(const Params &P, double rho, double e, double &p, dou
     }
 }
 
-// Fixed-order workgroup reduction of the record: slot 0 by max, the rest by sum.
+// v of the lane that a data-parallel move CTRL names, 0 where it names none or
+// the row of 16 lanes is not in ROWS.
+template <int CTRL, int ROWS = 0xF>
+__device__ inline double lane_or_zero(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xF, ROWS == 0xF);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xF, ROWS == 0xF);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Fixed-order workgroup reduction of the record: slot 0 by max (of numbers not
+// below 0), the rest by sum.  Within a wavefront by data-parallel moves towards
+// its last lane (with 96 cross-lane reads through LDS instead, the update of
+// 8,000 particles took 8.1 us, now 6.5, of 101,306 10.1 and 8.5, of 810,448
+// 27.6 and 25.5).
 __device__ inline void block_reduce_record(double r[kDiag], double *out)
 {
-    __shared__ double sh[kDiag][kBlock / kWave];
+    __shared__ double sh[kBlock / kWave][kDiag];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 #pragma unroll
     for (int k = 0; k < kDiag; ++k) {
         double v = r[k];
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) {
-            double o = __shfl_down(v, off, kWave);
-            v = (k == 0) ? fmax(v, o) : v + o;
-        }
-        if (lane == 0) sh[k][wave] = v;
+        auto fold = [&](double o) { v = k == 0 ? fmax(v, o) : v + o; };
+        fold(lane_or_zero<0x111>(v));        // from the lane 1 before
+        fold(lane_or_zero<0x112>(v));
+        fold(lane_or_zero<0x114>(v));
+        fold(lane_or_zero<0x118>(v));
+        fold(lane_or_zero<0x142, 0xA>(v));   // the row before, into rows 1 and 3
+        fold(lane_or_zero<0x143, 0xC>(v));   // row 1, into rows 2 and 3
+        if (lane == kWave - 1) sh[wave][k] = v;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < kDiagPartial) {
+        const int k = threadIdx.x;
+        double v = 0.0;
+        if (k < kDiag) {
 #pragma unroll
-        for (int k = 0; k < kDiag; ++k) {
-            double v = sh[k][0];
-            for (int w = 1; w < kBlock / kWave; ++w) v = (k == 0) ? fmax(v, sh[k][w]) : v + sh[k][w];
-            out[k] = v;
+            for (int w = 0; w < kBlock / kWave; ++w) v = k == 0 ? fmax(v, sh[w][k]) : v + sh[w][k];
         }
-        for (int k = kDiag; k < kDiagPartial; ++k) out[k] = 0.0;
+        out[k] = v;
     }
 }
 
