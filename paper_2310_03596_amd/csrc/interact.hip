@@ -44,8 +44,8 @@
 // wavefront instead of 26; 20.25 if no lane ever waited).  Measured per pass,
 // reads from L1 with their staging kernel first, whole windows in LDS second,
 // culled ones third: column FORCE FP32 401, 391, 350 us, FP64 675, 572, 520;
-// 4.0 M cylinder (FP32) FORCE 2.89, 2.59, 2.39 ms, GRADIENT 1.62, 1.50, 1.31;
-// 6.7 M impact (FP64) FORCE 8.83, 6.53, 6.15 ms, GRADIENT 4.02, 3.04, 2.80;
+// 4.0 M cylinder (FP32) FORCE 2.89, 2.59, 2.23 ms, GRADIENT 1.62, 1.50, 1.31;
+// 6.7 M impact (FP64) FORCE 8.83, 6.53, 5.95 ms, GRADIENT 4.02, 3.04, 2.80;
 // 250,047-particle FORCE reverse FP32 260, 248, 233 us; 27,000 ones FP64 FORCE
 // 54, 43, 39 us; 8,000 ones FP32 63, 33, 28 us (17 with 16 targets per workgroup).  Culling and loading in one
 // sweep instead of two was slower (441 us for the column's 373): each
@@ -125,19 +125,24 @@ struct Pass {
     static constexpr int NV = NR / C + (REST > 0 && !HALF ? 1 : 0);
     // Wavefronts per SIMD: caps the registers at 512 / that and the LDS of a
     // workgroup at 160 KB / that (LDS is given out in 1,280 bytes).  The most
-    // at which next to nothing is spilled (two registers; FP32 adjoint nine):
-    // one more is slower by 20 to 80 % (solid FORCE FP64 6.5 -> 12.2 ms, FP32
-    // adjoint 278 -> 502 us), one fewer by 2 to 30 %, as a page holds more but
-    // fewer wavefronts hide each other's waits.
-    static constexpr int waves_f32 = ADJ ? (SOLID ? 2 : 3) : (GADJ || (FORCE && SOLID) ? 3 : 4);
-    static constexpr int waves_f64 = ADJ ? (SOLID ? 1 : 2) : (GADJ || (FORCE && SOLID) ? 2 : 3);
+    // at which little is spilled (ten registers at most, outside the loop over
+    // hits): one more is slower by 20 to 80 % (FP32 adjoint 278 -> 502 us), one
+    // fewer by 2 to 30 %, as a page holds more but fewer wavefronts hide each
+    // other's waits.  Small calls of the solid FORCE pass, whose workgroups are
+    // all resident anyway, have one fewer and the larger page (13,824 FP64
+    // particles 27.3 us, 29.3 with three).
+    static constexpr bool FEW = FORCE && SOLID && TILE < 16;
+    static constexpr int waves_f32 = ADJ ? (SOLID ? 2 : 3) : (GADJ || FEW ? 3 : 4);
+    static constexpr int waves_f64 = ADJ ? (SOLID ? 1 : 2) : (GADJ || FEW ? 2 : 3);
     static constexpr int waves = SPLIT ? waves_f32 : waves_f64;
     // Records in flight while hits are evaluated: a second one costs registers
-    // and is worth them where a page's hits are few instructions apart or read
-    // many planes (measured on the bench's workloads: fluid FORCE FP32 420 us
-    // with two, 397 with one; FP64 598 and 563; FP32 adjoint 277 and 250; but
-    // GRADIENT FP32 1,498 and 1,537, solid FORCE FP64 6,570 and 6,650).
-    static constexpr bool kTwoAhead = GRAD || GADJ || (FORCE && SOLID);
+    // and is worth them where a page's hits are few instructions apart or where
+    // it costs no wavefront (GRADIENT FP32 1,498 us with two, 1,537 with one;
+    // fluid FORCE FP32 420 and 397, FP64 598 and 563, FP32 adjoint 277 and 250;
+    // solid FORCE 4 M FP32 2,406 with two and three wavefronts per SIMD, 2,225
+    // with one and four, 6.7 M FP64 6,160 with two and two, 5,950 with one and
+    // three).
+    static constexpr bool kTwoAhead = GRAD || GADJ || FEW;
     // Listed hits per target and round: above the 81 (and near misses) of a
     // lattice at h = 1.3 dx, since all may be in one page and a second round
     // lists them by a slower loop (64: column FP64 523 us, 8,000 FP32 particles
@@ -374,7 +379,7 @@ struct PairArgs {
 
 template <typename real, int PASS, bool SOLID, int TILE>
 __global__ __launch_bounds__(kPairBlock)
-__attribute__((amdgpu_waves_per_eu(Pass<real, PASS, SOLID>::waves)))
+__attribute__((amdgpu_waves_per_eu(Pass<real, PASS, SOLID, TILE>::waves)))
 void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, const uint32_t *__restrict__ ntdev,
              PV<real> src, const uint32_t *__restrict__ sstart, int zero_first, RV<real> R, RV<real> Rsrc, AV<real> B,
              Census cz)
@@ -1055,11 +1060,12 @@ hipError_t go(const Params &P, const Grid &g, const sph_particles &tg, const uin
     // 33, 19, 15; 8,000 28, 20, 17; 27,000 32, 28, 31; 46,656 37.5, 37.6, 45;
     // 64,000 41, 47, 57; solid FP64 FORCE of 4,096 30, 22, 14; 13,824 33, 27,
     // 30; its reverse (one workgroup per CU) 61, 38, 24 and 63, 65, 78.
-    constexpr uint32_t resident = kCUs * Pass<real, PASS, SOLID>::waves;
-    if (div_up(tg.n, Pass<real, PASS, SOLID, 4>::kGroup) <= resident)
-        launch(k_pairs<real, PASS, SOLID, 4>, Pass<real, PASS, SOLID, 4>::kGroup);
-    else if (div_up(tg.n, Pass<real, PASS, SOLID, 8>::kGroup) <= resident)
-        launch(k_pairs<real, PASS, SOLID, 8>, Pass<real, PASS, SOLID, 8>::kGroup);
+    using W4 = Pass<real, PASS, SOLID, 4>;
+    using W8 = Pass<real, PASS, SOLID, 8>;
+    if (div_up(tg.n, W4::kGroup) <= kCUs * W4::waves)
+        launch(k_pairs<real, PASS, SOLID, 4>, W4::kGroup);
+    else if (div_up(tg.n, W8::kGroup) <= kCUs * W8::waves)
+        launch(k_pairs<real, PASS, SOLID, 8>, W8::kGroup);
     else
         launch(k_pairs<real, PASS, SOLID, 16>, Pass<real, PASS, SOLID, 16>::kGroup);
     const hipError_t le = hipGetLastError();
