@@ -499,7 +499,7 @@ def main():
                    "n_particles": wl.n, "grid": wl.grid["dims"],
                    "form": "FP32 split (bucket index + float offset, pair sums accumulated in FP64; x, E in FP64)"
                    if main_prec == 1 else "plain FP64"},
-        "roofline": {"bound": "alu", "kernel": "FORCE pass pair kernel (k_pairs, staging excluded)",
+        "roofline": {"bound": "alu", "kernel": "FORCE pass pair kernel (k_pairs)",
                      "achieved": r["force_tflops"], "peak": PEAK_TFLOPS[main_prec], "unit": "TFLOP/s",
                      "frac": r["force_tflops"] / PEAK_TFLOPS[main_prec], "traffic": recorded_traffic(main_prec),
                      "avg_launch_ms": r["force_ms"], "flops_per_launch": r["flops_per_launch"],

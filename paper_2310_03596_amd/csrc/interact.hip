@@ -152,7 +152,7 @@ struct Pass {
     // LDS has room for (up to 20 rows: a page of 16 held GRADIENT at 1.38 ms for
     // 1.31; with 24 its lists and words cost more than the page gains).  The
     // hit lists take the place of the candidate operands once these have been
-    // read, which is worth a barrier: one page holds 440 sources instead of 336
+    // read, which is worth a barrier: one page holds 432 sources instead of 336
     // (column FP32 352 -> 344 us).  Rows start in different LDS banks (odd
     // pitch), and so do the candidate operands that 16 lanes read together
     // (pitch 4 or 12 modulo 16).
@@ -394,12 +394,13 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
     using half = typename Chunk<real>::half;
     __shared__ full plane[W::NV][kRows * kPitch];
     __shared__ half plane_h[W::HALF ? kRows * kPitch : 1];
-    // the candidate operands (q, |q|^2) of the page's sources, then the hit lists
+    // the candidate operands (q, |q|^2) of the page's sources, then the hit
+    // lists, at the end the targets' sums
     __shared__ alignas(16) unsigned char shared[W::kShared];
     f32x4 *const cand = reinterpret_cast<f32x4 *>(shared);
     uint16_t *const list = reinterpret_cast<uint16_t *>(shared);
-    __shared__ uint16_t kept_of[kBatch];                  // the window's entries near the group, a segment per wavefront
-    __shared__ uint32_t kept_n[kPairWaves];
+    __shared__ uint16_t kept_of[kBatch];      // the window's entries near the group, a segment per wavefront
+    __shared__ uint32_t kept_n[kPairWaves];   // and how many each holds
     constexpr int kListPitch = W::kListPitch;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);

@@ -46,8 +46,8 @@ class TwoSets:
         self.n = wl.n
         s0 = self.sides[0]
         self.params, self.grid, self.nc = s0.params, s0.grid, s0.nc
-        # one workspace for every call (sized for the larger set: a local-remote
-        # pass stages the other set's particles)
+        # one workspace for every call (sized for the larger set, as every call
+        # checks it against its own arrays)
         nmax = max(wa.n, wb.n, 1)
         self.ws_bytes = L.sph_workspace_size(self.grid, nmax, prec, L.SPH_FLUID_TAIT)
         self.ws = torch.zeros(self.ws_bytes, dtype=torch.uint8, device=device)

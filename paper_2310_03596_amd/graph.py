@@ -1,7 +1,8 @@
 """A step loop captured as one HIP graph.
 
 Small workloads (the 8,000-particle cube) are bound by kernel launches: a
-fluid step is about thirteen launches of a few microseconds each.  The
+fluid step is six launches of a few microseconds each (up to eleven on
+larger grids).  The
 library's calls only enqueue work on the caller's stream, allocate nothing
 and never synchronise, so a run of steps can be captured once (through
 PyTorch's graph capture, on its capture stream) and replayed with one launch
