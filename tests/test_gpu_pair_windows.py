@@ -1,7 +1,7 @@
 """The pair kernel at the edges of its tiles, pages and hit lists: target
 counts around 16 (a wavefront's targets) and 64 (a workgroup's), windows of
-more sources than one page of any variant holds (at most 512) with more hits
-per target than one round of its list (64), and target lists in any order.
+more sources than one page of any variant holds (at most 640) with more hits
+per target than one round of its list (96), and target lists in any order.
 
 Neighbour sets are compared exactly (tests/census.py); the pair sums of the
 variants whose pages differ from the census's with the oracle, within the
