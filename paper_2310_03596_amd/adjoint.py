@@ -40,30 +40,20 @@ class Cotangent(_Flat):
                        + [(f, (n,), real) for f in ("m", "w", "E", "rho", "p", "c", "e")]
                        + [("S", (6, n) if solid else None, real), ("ep", (n,) if solid else None, real)], device)
 
-    def _bind(self):
-        super()._bind()
+    def _forget(self):
+        super()._forget()
         self._state = None
 
     def _make_struct(self, scalars) -> L.SphAdjoint:
         a = L.SphAdjoint()
-        if self.n == 0:
-            return a
-        for name in ("x", "v", "S"):
-            to = getattr(a, name)
-            for k, ptr in enumerate(self._addresses(name)):
-                to[k] = ptr
-        base = self._buf.data_ptr()
-        for name, field in scalars:
-            at = self._fields[field]
-            if at is not None:
-                setattr(a, name, base + at[0])
+        self._point(a, ("x", "v", "S"), scalars)
         return a
 
     STATE = (("m", "m"), ("omega", "w"), ("E", "E"), ("eps_p", "ep"))
     DERIVED = (("rho", "rho"), ("p", "p"), ("c", "c"), ("e", "e"))
 
     def struct(self) -> L.SphAdjoint:
-        """The ABI struct of these buffers (built once: they never move)."""
+        """The ABI struct of these buffers (kept: they never move)."""
         if self._struct is None:
             self._struct = self._make_struct(self.STATE + self.DERIVED)
         return self._struct

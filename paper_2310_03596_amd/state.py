@@ -78,20 +78,27 @@ class _Flat:
     A field's tensor is made when it is first asked for, and the ABI structs
     from the buffer's address and the field's place in it: a rollout and its
     reverse pass make dozens of such sets and read only the structs (a
-    27,000-particle gradient of ten steps: 5.1 -> 3.6 ms)."""
+    27,000-particle gradient of ten steps: 5.1 -> 3.6 ms).  A tensor that a
+    program assigns to a field takes the place of the buffer's part, in the
+    structs too."""
 
     def _allocate(self, layout, device, zero=True):
         """zero=False leaves the memory uninitialised (no fill kernel), for
         buffers that a call overwrites completely before anything reads them."""
-        self._fields, nbytes = _plan(tuple(layout))
+        fields, nbytes = _plan(tuple(layout))
         alloc = torch.zeros if zero else torch.empty
         self._buf = alloc(nbytes, dtype=torch.uint8, device=device)
+        self._fields = fields
         self._bind()
 
     def _bind(self):
         for k in self._fields:
             self.__dict__.pop(k, None)
-        self._struct = None   # the ABI struct of these buffers, built on first use
+        self._assigned = frozenset()   # fields whose tensors are the program's own
+        self._forget()
+
+    def _forget(self):
+        self._struct = None   # the ABI struct, built on first use
 
     def __getattr__(self, name):
         fields = self.__dict__.get("_fields")
@@ -102,25 +109,71 @@ class _Flat:
         self.__dict__[name] = t
         return t
 
-    def _addresses(self, name):
-        """Device addresses of the entries of a field's first axis; none if the
-        set has no such field."""
-        at = self._fields.get(name)
-        if at is None or at[1] == 0:
+    def __setattr__(self, name, value):
+        field = name in self.__dict__.get("_fields", ())
+        if field and value is self.__dict__.get(name, self):   # p.x += t
+            return
+        self.__dict__[name] = value
+        if field:
+            self._assigned |= {name}
+            self._forget()
+
+    def __getstate__(self):
+        """What a copy or a file holds: no struct, whose addresses are this
+        set's, and no view of the buffer."""
+        state = {k: v for k, v in self.__dict__.items() if k not in self._fields or k in self._assigned}
+        state.update((k, None) for k in ("_struct", "_state") if k in state)
+        return state
+
+    def _address(self, name):
+        """Device address of a field; None if the set has no such field or it is empty."""
+        if name in self._assigned:
+            t = self.__dict__[name]
+            return None if t is None or t.numel() == 0 else t.data_ptr()
+        at = self._fields[name]
+        return None if at is None or at[1] == 0 else self._buf.data_ptr() + at[0]
+
+    def _addresses(self, name, count):
+        """Device addresses of the first `count` entries of a field's first
+        axis; none if the set has no such field or it is empty."""
+        base = self._address(name)
+        if base is None:
             return ()
-        base = self._buf.data_ptr() + at[0]
-        return range(base, base + at[1], at[4])
+        if name in self._assigned:
+            t = self.__dict__[name]
+            return [t[k].data_ptr() for k in range(count)]
+        step = self._fields[name][4]
+        return range(base, base + count * step, step)
+
+    def _point(self, struct, arrays, scalars):
+        """Point a struct's members at the fields: arrays by their common
+        name, scalars as (member, field)."""
+        for name in arrays:
+            to = getattr(struct, name)
+            for k, ptr in enumerate(self._addresses(name, len(to))):
+                to[k] = ptr
+        for member, name in scalars:
+            setattr(struct, member, self._address(name))
 
     def clone(self):
         """A copy with its own storage (one device copy)."""
         q = copy.copy(self)
         q._buf = self._buf.clone()
         q._bind()
+        for name in self._assigned:
+            t = self.__dict__[name]
+            setattr(q, name, None if t is None else t.clone())
         return q
 
     def copy_from(self, other):
         """Overwrite every field with other's (same sizes; one device copy)."""
-        self._buf.copy_(other._buf)
+        if not (self._assigned or other._assigned):
+            self._buf.copy_(other._buf)
+            return
+        for name in self._fields:
+            to = getattr(self, name)
+            if to is not None:
+                to.copy_(getattr(other, name))
 
 
 class Particles(_Flat):
@@ -139,8 +192,11 @@ class Particles(_Flat):
                    ("ep", (n,) if solid else None, real)]
         self._allocate(layout, device, zero)
 
+    STRUCT = (("hash", "hash"), ("id", "id"), ("m", "m"), ("omega", "w"), ("rho", "rho"), ("p", "p"), ("c", "c"),
+              ("e", "e"), ("E", "E"))
+
     def struct(self) -> L.SphParticles:
-        """The ABI struct of this array (built once: the buffers never move)."""
+        """The ABI struct of this array (kept: the buffers never move)."""
         if self._struct is None:
             self._struct = self._make_struct()
         return self._struct
@@ -151,17 +207,9 @@ class Particles(_Flat):
         s.prec = self.prec
         if self.n == 0:
             return s
-        for name in ("x", "off", "v", "S"):
-            to = getattr(s, name)
-            for k, ptr in enumerate(self._addresses(name)):
-                to[k] = ptr
-        base, at = self._buf.data_ptr(), self._fields
-        s.hash, s.id = base + at["hash"][0], base + at["id"][0]
-        s.m, s.omega, s.rho = base + at["m"][0], base + at["w"][0], base + at["rho"][0]
-        s.p, s.c, s.e = base + at["p"][0], base + at["c"][0], base + at["e"][0]
-        s.E = base + at["E"][0]
+        self._point(s, ("x", "off", "v"), self.STRUCT)
         if self.solid:
-            s.eps_p = base + at["ep"][0]
+            self._point(s, ("S",), (("eps_p", "ep"),))
         return s
 
     @classmethod
@@ -212,10 +260,7 @@ class Rates(_Flat):
 
     def _make_struct(self) -> L.SphRates:
         r = L.SphRates()
-        for name in ("hi", "lo", "Lhi", "Llo"):
-            to = getattr(r, name)
-            for k, ptr in enumerate(self._addresses(name)):
-                to[k] = ptr
+        self._point(r, ("hi", "lo", "Lhi", "Llo"), ())
         return r
 
     def force(self) -> torch.Tensor:
