@@ -554,7 +554,7 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
         }
     };
     constexpr int kRec = W::NV * C + (W::HALF ? C / 2 : 0);
-    const float kFar = 1e30f;
+    const float kFar = __builtin_inff();   // of no source, and of no target: above any bound, in any unit of length
 
     while (pending) {
         // the next group: targets that share the first pending target's bucket row
