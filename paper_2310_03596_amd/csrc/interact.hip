@@ -7,7 +7,13 @@
 //
 // Work mapping (k_pairs): a workgroup of four wavefronts takes 64
 // consecutive targets (32 or 16 where the call is small), in groups that share
-// a bucket row (cy, cz); consecutive sorted targets almost always do.
+// a bucket row (cy, cz); consecutive sorted targets often do.
+//   * Up to four groups are taken together where their windows are short enough:
+//     one after the other, each would go through the chain of loads and barriers
+//     below for its few targets.  (One by one and together, in us: FORCE of a gas
+//     of 30,000 particles at one a bucket FP32 43 and 25, FP64 70 and 33; at 0.05 a
+//     bucket 66 and 34, 118 and 52; of a shuffled list of 30,000 particles 222 and
+//     158; the step of a lattice of 101,306 FP32 particles 98.7 and 88.3.)
 //   * The window of a group is the 9 neighbour rows over the union of its
 //     targets' buckets, about 800 sources on a lattice.  The workgroup first
 //     reads their positions and culls those that are farther than 2h from the
@@ -24,8 +30,11 @@
 //     and the pair body (about a hundred operations) are kept apart, and the
 //     body runs dense.  (One lane per target would leave the chip idle below
 //     some 60,000 particles, and wait for its busiest lane.)
-// The lanes' sums are added at the end.  The order of summation depends
-// on the particles' order and number alone, so repeated calls agree bit for bit.  A pair
+// The lanes' sums are added at the end.  The order of summation depends on
+// the number of targets (which sets the lanes per target), on what other targets a
+// workgroup has and on all positions (which set what a page holds), so a target
+// listed and the same target in a pass over its whole array may differ by
+// rounding; calls with the same arrays, counts and list agree bit for bit.  A pair
 // with r = 0 (the target itself, or a coincident particle) adds nothing: its
 // terms all carry F(0) = 0.
 //
@@ -58,6 +67,7 @@
 // gfx950: a convert and an add per term) and are stored as a float (hi, lo)
 // pair.
 #include <atomic>
+#include <cmath>
 
 #include "pair.hpp"
 
@@ -74,10 +84,9 @@ constexpr uint32_t kCUs = 256;
 // Sources in flight per lane while the window is culled (column FP32: 1 364,
 // 2 362, 4 368 us).
 constexpr int kAhead = 2;
-constexpr int kSeg = 384;                         // entries of a batch that a wavefront looks at
-constexpr int kBatch = kPairWaves * kSeg;         // window entries culled at a time (a lattice's windows: 800 to 1,450)
+constexpr int kBatch = 1536;                      // window entries culled at a time (a lattice's windows: 800 to 1,450)
 constexpr int kEntryBits = 11;                    // of a kept entry's code: its place in the batch, then its row
-static_assert(kBatch <= 1 << kEntryBits && kSeg % (kWave * kAhead) == 0, "a batch's entries");
+static_assert(kBatch <= 1 << kEntryBits, "a batch's entries");
 constexpr int kPassAdjoint = 2;            // reverse mode of the FORCE pass
 constexpr int kPassGradAdjoint = 4;        // reverse mode of the GRADIENT pass
 constexpr int kPassCensus = 3;             // neighbour census of a FORCE or GRADIENT pass
@@ -213,6 +222,14 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The lanes where b holds (a lane mask as the compare leaves it: __ballot's int
+// costs two more vector instructions).
+__device__ inline uint64_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+
+// a / d, where inv is (1 + 2^-50) / d: the product exceeds a / d by up to
+// 2^-17 / d, and a / d is at least 1 / d below the next integer.
+__device__ inline uint32_t udiv(uint32_t a, double inv) { return (uint32_t)((double)a * inv); }
+
 // A wave-uniform double held in scalar registers (it is an operand of
 // vector instructions, so it takes no vector registers of its own).
 __device__ inline double uniform_double(double v)
@@ -238,7 +255,7 @@ __device__ inline int wave_max_u7(int v)
 #pragma unroll
     for (int b = 6; b >= 0; --b) {
         const int c = r | (1 << b);
-        if (__ballot(v >= c)) r = c;
+        if (ballot(v >= c)) r = c;
     }
     return r;
 }
@@ -325,50 +342,6 @@ struct Chunk<double> {
     using half = double __attribute__((ext_vector_type(1)));
 };
 
-// Entry j of a field, by a 32-bit byte offset from its base (sources are fewer
-// than 2^27), so that the loads of all fields share one address register.
-template <typename T>
-__device__ inline T field(const T *base, uint32_t j)
-{
-    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + j * (uint32_t)sizeof(T));
-}
-
-// The fields of source j that a pass reads, in record order.
-template <typename real, int PASS, bool SOLID>
-__device__ inline void load_fields(const PV<real> &s, const RV<real> &rb, const Census &cz, uint32_t j, real *f)
-{
-    using W = Pass<real, PASS, SOLID>;
-    if constexpr (W::CENSUS) {
-        if constexpr (W::SPLIT)
-            f[0] = __builtin_bit_cast(float, field(cz.sid, j));
-        else
-            f[0] = __builtin_bit_cast(double, (uint64_t)field(cz.sid, j));
-    } else {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) f[d] = field(s.v[d], j);
-        f[3] = field(s.w, j);
-        if constexpr (W::FORCE || W::ADJ) {
-            f[4] = field(s.rho, j);
-            f[5] = field(s.p, j);
-            f[6] = field(s.c, j);
-            f[7] = field(s.e, j);
-            if constexpr (SOLID) {
-#pragma unroll
-                for (int k = 0; k < 6; ++k) f[8 + k] = field(s.S[k], j);
-            }
-        }
-        // cotangents of the sources' rates or velocity gradients (none: zero)
-        if constexpr (W::ADJ) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) f[(SOLID ? 14 : 8) + k] = rb.hi[0] ? field(rb.hi[k], j) : real(0);
-        }
-        if constexpr (W::GADJ) {
-#pragma unroll
-            for (int k = 0; k < 9; ++k) f[4 + k] = rb.Lhi[0] ? field(rb.Lhi[k], j) : real(0);
-        }
-    }
-}
-
 // Constants of a pass, made on the host so that they are scalar operands.
 template <typename real>
 struct PairArgs {
@@ -377,12 +350,96 @@ struct PairArgs {
     float h2;   // 2h
 };
 
+// Arguments of a call.
+template <typename real>
+struct PairCall {
+    PairArgs<real> A;
+    Grid g;
+    PV<real> tg;
+    const uint32_t *tidx, *ntdev;
+    PV<real> src;
+    const uint32_t *sstart;
+    double nx_inv, ny_inv;   // for udiv by the grid's nx and ny
+    real Linv;               // 1 / L, no number where L is not between 2^-60 and 2^45
+    int zero_first;
+    RV<real> R, Rsrc;
+    AV<real> B;
+    Census cz;
+};
+template <typename real>
+using CallArgs = const __attribute__((address_space(4))) PairCall<real> *;
+
+// The kernel's arguments, read again where they are used.  Some 40 pointers and
+// constants that stay in scalar registers from one use to the next push the loops'
+// own scalars out into vector registers (50 to 120 of them, and up to 23 vector
+// registers out into scratch, against 0 to 15 and up to 15: column FORCE FP32 356
+// and 339 us, a share's sort and two passes 1,393 and 1,305).
+template <typename real>
+__device__ inline CallArgs<real> call_args()
+{
+    auto a = (CallArgs<real>)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return a;
+}
+
+// Entry j of a field, by a 32-bit byte offset from its base (sources are fewer
+// than 2^27), so that the loads of all fields share one address register.
+template <typename T>
+__device__ inline T field(const T *base, uint32_t j)
+{
+    using Byte = const __attribute__((address_space(1))) char *;
+    using Entry = const __attribute__((address_space(1))) T *;
+    return *(Entry)((Byte)base + j * (uint32_t)sizeof(T));
+}
+
+// Entry j of a field of any length, through a pointer read by call_args (of
+// which the compiler would not know that it points to global memory).
+template <typename T>
+__device__ inline __attribute__((address_space(1))) T &entry(T *base, uint32_t j)
+{
+    return ((__attribute__((address_space(1))) T *)base)[j];
+}
+
+// The fields of source j that a pass reads, in record order.
+template <typename real, int PASS, bool SOLID>
+__device__ inline void load_fields(CallArgs<real> a, uint32_t j, real *f)
+{
+    using W = Pass<real, PASS, SOLID>;
+    if constexpr (W::CENSUS) {
+        if constexpr (W::SPLIT)
+            f[0] = __builtin_bit_cast(float, field(a->cz.sid, j));
+        else
+            f[0] = __builtin_bit_cast(double, (uint64_t)field(a->cz.sid, j));
+    } else {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) f[d] = field(a->src.v[d], j);
+        f[3] = field(a->src.w, j);
+        if constexpr (W::FORCE || W::ADJ) {
+            f[4] = field(a->src.rho, j);
+            f[5] = field(a->src.p, j);
+            f[6] = field(a->src.c, j);
+            f[7] = field(a->src.e, j);
+            if constexpr (SOLID) {
+#pragma unroll
+                for (int k = 0; k < 6; ++k) f[8 + k] = field(a->src.S[k], j);
+            }
+        }
+        // cotangents of the sources' rates or velocity gradients (none: zero)
+        if constexpr (W::ADJ) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) f[(SOLID ? 14 : 8) + k] = a->Rsrc.hi[0] ? field(a->Rsrc.hi[k], j) : real(0);
+        }
+        if constexpr (W::GADJ) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) f[4 + k] = a->Rsrc.Lhi[0] ? field(a->Rsrc.Lhi[k], j) : real(0);
+        }
+    }
+}
+
 template <typename real, int PASS, bool SOLID, int TILE>
 __global__ __launch_bounds__(kPairBlock)
 __attribute__((amdgpu_waves_per_eu(Pass<real, PASS, SOLID, TILE>::waves)))
-void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__ tidx, const uint32_t *__restrict__ ntdev,
-             PV<real> src, const uint32_t *__restrict__ sstart, int zero_first, RV<real> R, RV<real> Rsrc, AV<real> B,
-             Census cz)
+void k_pairs(PairCall<real> call)
 {
     using W = Pass<real, PASS, SOLID, TILE>;
     constexpr bool SPLIT = W::SPLIT, ADJ = W::ADJ, GADJ = W::GADJ, CENSUS = W::CENSUS, FORCE = W::FORCE;
@@ -400,15 +457,19 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
     f32x4 *const cand = reinterpret_cast<f32x4 *>(shared);
     uint16_t *const list = reinterpret_cast<uint16_t *>(shared);
     __shared__ uint16_t kept_of[kBatch];      // the window's entries near the group, a segment per wavefront
-    __shared__ uint32_t kept_n[kPairWaves];   // and how many each holds
+    __shared__ uint32_t kept_n[kPairWaves];   // and how many each holds, and of how many looked at
+    __shared__ double corner_of[SPLIT ? 1 : kPairWaves][3];   // the frames of groups taken together (FP64 form)
     constexpr int kListPitch = W::kListPitch;
 
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave0 = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const PV<real> &tg = call.tg;
+    const uint32_t *const tidx = call.tidx;
+    const bool listed = tidx != nullptr;
     uint32_t nt = tg.n, tile;
-    if (tidx) {
+    if (listed) {
         // a target list's count is on the device and the grid is sized for the
         // whole array: the list's tiles shared evenly by the XCDs
-        const uint32_t c = *ntdev;
+        const uint32_t c = *call.ntdev;
         nt = c < nt ? c : nt;
         if (!xcd_tile_active(blockIdx.x, (nt + kGroup - 1) / kGroup, tile)) return;
     } else {
@@ -416,35 +477,45 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
     }
     // lane l of every wavefront looks at target l of the workgroup
     const uint32_t t = tile * (uint32_t)kGroup + (uint32_t)lane;
-    uint32_t ti = lane < kGroup && t < nt ? (tidx ? tidx[t] : t) : tg.n;
+    uint32_t ti = lane < kGroup && t < nt ? (listed ? tidx[t] : t) : tg.n;
     const bool tvalid = ti < tg.n;   // a listed index outside the target array names no target
     ti = tvalid ? ti : 0u;
     const uint32_t th = tg.hash[ti];
-    const uint32_t trow = th / (uint32_t)g.nx;   // cy + ny cz
-    const int tcx = (int)(th - trow * (uint32_t)g.nx);
+    uint32_t trow = udiv(th, call.nx_inv);   // cy + ny cz
+    const int tcx = (int)(th - trow * (uint32_t)call.g.nx);
+    trow = tvalid ? trow : ~0u;   // no target's row: there are fewer buckets than 2^32 - 1
     // the lane's target in the candidate test, and the one whose pairs it evaluates
     // (of a test's 16 columns, the first TILE hold targets)
-    const int lf = wave * TILE + (lane & (TILE - 1)), le = wave * TILE + lane / kShare;
-    const int sub = lane & (kShare - 1), quarter = lane / 16;
+    const int lf = wave0 * TILE + (lane & (TILE - 1)), le = wave0 * TILE + lane / kShare;
+    const int sub = lane & (kShare - 1);
     const uint32_t i = __shfl(ti, le, kWave);
     const int ecx = __shfl(tcx, le, kWave);
-    uint64_t pending = __ballot(tvalid);
+    uint64_t pending = ballot(tvalid);
     const bool valid = (pending >> le) & 1ull;
 
-    const PairK<real> &K = A.K;
-    const real R2 = A.R2;
+    PairK<real> K;
+    real R2;
 
     TargetPos<real> T;
-    T.Lf = SPLIT ? (real)g.Lf : real(0);
+    real tpos[3];   // of the lane's target
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         if constexpr (SPLIT) {
+            tpos[d] = tg.off[d][ti];
             T.o[d] = tg.off[d][i];
             T.x[d] = 0.0;
         } else {
+            tpos[d] = tg.x[d][ti];
             T.x[d] = tg.x[d][i];
             T.o[d] = real(0);
         }
+    }
+    // Listed targets need not ascend; where they do, a group's outer buckets are
+    // those of its first and last target.
+    bool ascend = true;
+    if (listed) {
+        const uint32_t before = __shfl_up(th, 1, kWave);
+        ascend = !ballot(lane > 0 && tvalid && th < before);
     }
     Part<real, SOLID> I;
     real rbi[GADJ ? 9 : 6];   // adjoint: the target's rate (or velocity-gradient) cotangents
@@ -457,11 +528,11 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
     }
     if constexpr (ADJ) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k) rbi[k] = R.hi[0] ? R.hi[k][i] : real(0);
+        for (int k = 0; k < 6; ++k) rbi[k] = call.R.hi[0] ? call.R.hi[k][i] : real(0);
     }
     if constexpr (GADJ) {
 #pragma unroll
-        for (int k = 0; k < 9; ++k) rbi[k] = R.Lhi[0] ? R.Lhi[k][i] : real(0);
+        for (int k = 0; k < 9; ++k) rbi[k] = call.R.Lhi[0] ? call.R.Lhi[k][i] : real(0);
     }
 
     Acc acc[NOUT];
@@ -557,17 +628,176 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
     const float kFar = __builtin_inff();   // of no source, and of no target: above any bound, in any unit of length
 
     while (pending) {
-        // the next group: targets that share the first pending target's bucket row
-        const int leader = __ffsll((unsigned long long)pending) - 1;
-        const uint32_t key = __builtin_amdgcn_readlane(trow, leader);
-        const bool tin = tvalid && trow == key;
-        const uint64_t in64 = __ballot(tin);
-        pending &= ~in64;
-        const int lcx = __builtin_amdgcn_readlane(tcx, leader);   // origin of the group's frame along x
-        const int gz = (int)(key / (uint32_t)g.ny), gy = (int)(key - (uint32_t)gz * (uint32_t)g.ny);
-        const bool fin = (lane & 15) < TILE && (in64 >> lf) & 1ull;
-        const uint32_t in_tile = (uint32_t)(in64 >> (wave * TILE)) & ((1u << TILE) - 1u);
-        T.cxf = (real)(ecx - lcx);
+        // (What depends on these alone is made anew in each round, not kept.)
+        int quarter = lane / 16, wave = wave0;
+        asm volatile("" : "+v"(quarter));
+        asm volatile("" : "+s"(wave));
+        const CallArgs<real> at_round = call_args<real>();
+        const auto &g = at_round->g;
+        T.Lf = SPLIT ? (real)g.Lf : real(0);
+        // The next groups, of targets that share a bucket row: the first pending
+        // target's and up to three more.  Lanes 16 k .. 16 k + 15 keep what
+        // concerns group k: its row, the bucket its frame starts at, its buckets.
+        uint64_t in64[kPairWaves];
+        uint32_t ng = 0, wkey = 0;
+        int wcx = 0, wx1 = 0;
+        uint64_t rest = pending;
+#pragma unroll
+        for (int k = 0; k < kPairWaves; ++k) {
+            in64[k] = 0;
+            if (rest) {
+                const int first = __ffsll((unsigned long long)rest) - 1;
+                const uint32_t key = __builtin_amdgcn_readlane(trow, first);
+                in64[k] = ballot(trow == key);
+                rest &= ~in64[k];
+                const int c0 = __builtin_amdgcn_readlane(tcx, first);
+                const int c1 = __builtin_amdgcn_readlane(tcx, 63 - __clzll((long long)in64[k]));
+                wkey = quarter == k ? key : wkey;
+                wcx = quarter == k ? c0 : wcx;
+                wx1 = quarter == k ? c1 : wx1;
+                ng = (uint32_t)k + 1u;
+            }
+        }
+        int wx0 = wcx;
+        if (!ascend) {
+            uint32_t most[kPairWaves], least[kPairWaves];
+#pragma unroll
+            for (int k = 0; k < kPairWaves; ++k) {
+                const bool in = (in64[k] >> lane) & 1ull;
+                most[k] = in ? (uint32_t)tcx : 0u;
+                least[k] = in ? ~(uint32_t)tcx : 0u;
+            }
+            wave_max4(most);
+            wave_max4(least);
+#pragma unroll
+            for (int k = 0; k < kPairWaves; ++k) {
+                wx0 = quarter == k ? (int)~least[k] : wx0;
+                wx1 = quarter == k ? (int)most[k] : wx1;
+            }
+        }
+        if (ng > 1) {
+            // Frames that lie apart along x, so that no source of one group passes the
+            // candidate test of another's target: its d would be meaningless.  The groups
+            // are taken together only if their targets are at most half a bucket outside
+            // their own buckets; what culling keeps is at most 2h beyond those, but for
+            // the margins, 2^-16 of the square of the frames' length T (1.2 sum W + 50
+            // buckets, W their widths) and in FP64 less than T / 64 squared buckets.  The
+            // gap of 8 + sum W / 32 buckets leaves room for these and for the test's.
+            uint32_t w[kPairWaves], sum = 0, from = 0;
+#pragma unroll
+            for (int k = 0; k < kPairWaves; ++k) {
+                w[k] = (uint32_t)__builtin_amdgcn_readlane(wx1 - wx0, 16 * k) + 1u;
+                sum += (uint32_t)k < ng ? w[k] : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < kPairWaves; ++k) {
+                wcx = quarter == k ? wx0 - (int)from : wcx;
+                from += w[k] + 8u + sum / 32u;
+            }
+            if (sum > 4096u) ng = 1;   // (squares of the frame's lengths stay finite)
+        }
+        // Their windows: lane 16 k + r, r < 9, keeps row r of group k's, which holds
+        // entries [off, off + n) of it; entry u is source u + del
+        const int wgz = (int)udiv(wkey, at_round->ny_inv), wgy = (int)(wkey - (uint32_t)wgz * (uint32_t)g.ny);
+        const int wr = lane & 15, wrz = (wr * 11) >> 5;
+        uint32_t wub = 0, wn = 0;
+        {
+            const int xa = wx0 > 0 ? wx0 - 1 : 0, xb = wx1 + 1 < g.nx ? wx1 + 1 : g.nx - 1;
+            const int z = wgz + wrz - 1, y = wgy + (wr - 3 * wrz) - 1;
+            if (wr < 9 && (uint32_t)quarter < ng && z >= 0 && z < g.nz && y >= 0 && y < g.ny) {
+                const uint32_t row = (uint32_t)g.nx * ((uint32_t)y + (uint32_t)g.ny * (uint32_t)z);
+                wub = entry(at_round->sstart, row + (uint32_t)xa);
+                wn = entry(at_round->sstart, row + (uint32_t)xb + 1u) - wub;
+            }
+        }
+        uint32_t woff = wn;   // sums over rows 0 .. r of the window
+        woff += (uint32_t)dpp<0x111>(0, (int)woff);
+        woff += (uint32_t)dpp<0x112>(0, (int)woff);
+        woff += (uint32_t)dpp<0x114>(0, (int)woff);
+        woff += (uint32_t)dpp<0x118>(0, (int)woff);
+        uint32_t tot[kPairWaves];
+#pragma unroll
+        for (int k = 0; k < kPairWaves; ++k) tot[k] = __builtin_amdgcn_readlane(woff, 16 * k + 8);
+        woff -= wn;
+        const uint32_t wdel = wub - woff;
+        // hash of bucket wcx of the lane's row of the window
+        const uint32_t rhash = wkey * (uint32_t)g.nx + (uint32_t)wcx +
+                               (uint32_t)g.nx * ((uint32_t)(wr - 3 * wrz - 1) + (uint32_t)g.ny * (uint32_t)(wrz - 1));
+        // Groups whose windows fit one batch are taken together; otherwise the
+        // first alone.  The wavefronts that cull a group's window: two for the
+        // largest of three, or those of two that share the work best; gm holds
+        // each wavefront's group, two bits of it.
+        uint32_t all = tot[0], gm = 0;
+        uint64_t act = in64[0];
+        if (ng > 1) {
+            // With targets that are outside their buckets (beyond the grid, whose
+            // outer buckets hold what is), or a grid too far from the origin, or a bucket
+            // side near the ends of the floats' range (Linv is no number), one alone.
+            bool astray = false;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                if constexpr (SPLIT) {
+                    const float q = tpos[d] * at_round->Linv;
+                    astray = astray || !(q > -0.5f && q < 1.5f);
+                } else {
+                    const uint32_t y = udiv(trow, at_round->ny_inv);
+                    const uint32_t c = d == 0 ? (uint32_t)tcx : (d == 1 ? trow - y * (uint32_t)g.ny : y);
+                    const double o = g.o[d] + (double)c * g.L, q = (tpos[d] - o) * at_round->Linv;
+                    astray = astray || !(q > -0.5 && q < 1.5 && fabs(o) * at_round->Linv < 0x1p38);
+                }
+            }
+            uint32_t taken = 1;
+            bool fit = !ballot(tvalid && astray);
+#pragma unroll
+            for (int k = 1; k < kPairWaves; ++k) {
+                fit = fit && (uint32_t)k < ng && all + tot[k] <= (uint32_t)kBatch;
+                if (fit) {
+                    all += tot[k];
+                    act |= in64[k];
+                    ++taken;
+                }
+            }
+            if (taken == 4)
+                gm = 0xE4;   // 3 2 1 0
+            else if (taken == 3)
+                gm = tot[0] >= max(tot[1], tot[2]) ? 0x90 : (tot[1] >= tot[2] ? 0x94 : 0xA4);   // 2 1 0 0, 2 1 1 0, 2 2 1 0
+            else if (taken == 2)
+                gm = tot[0] > 2 * tot[1] ? 0x40 : (tot[1] > 2 * tot[0] ? 0x54 : 0x50);   // 1 0 0 0, 1 1 1 0, 1 1 0 0
+        }
+        const bool multi = gm != 0;
+        pending &= ~act;
+        // This wavefront's group, how many share it and which of them it is, the
+        // entries of its window, and the place of the first in the batch
+        int gs = 0;
+        uint32_t nw = kPairWaves, iw = (uint32_t)wave, total = tot[0], place0 = 0;
+        uint64_t ins = in64[0];
+        if (multi) {
+            gs = (int)(gm >> (2 * wave)) & 3;
+            nw = iw = 0;
+#pragma unroll
+            for (int k = 0; k < kPairWaves; ++k) {
+                const bool same = (int)(gm >> (2 * k) & 3u) == gs;
+                nw += same ? 1u : 0u;
+                iw += same && k < wave ? 1u : 0u;
+                place0 += k < gs ? tot[k] : 0u;
+                total = k == gs ? tot[k] : total;
+                ins = k == gs ? in64[k] : ins;
+            }
+        }
+        const bool tin = (ins >> lane) & 1ull;
+        const int lcx = __builtin_amdgcn_readlane(wcx, 16 * gs);   // origin of the group's frame along x
+        const int gy = __builtin_amdgcn_readlane(wgy, 16 * gs), gz = __builtin_amdgcn_readlane(wgz, 16 * gs);
+        const bool fin = (lane & 15) < TILE && (act >> lf) & 1ull;
+        const uint32_t in_tile = (uint32_t)(act >> (wave * TILE)) & ((1u << TILE) - 1u);
+        int og = 0, ocx = lcx;   // the group of the lane's target, and its frame's origin along x
+        if (multi) {
+#pragma unroll
+            for (int k = 1; k < kPairWaves; ++k) og = (in64[k] >> lane) & 1ull ? k : og;
+            ocx = __shfl(wcx, 16 * og, kWave);
+            T.cxf = (real)(ecx - __shfl(ocx, le, kWave));
+        } else {
+            T.cxf = (real)(ecx - lcx);
+        }
         // Frame of the candidate test, in FP32 in both forms: positions relative
         // to the corner of bucket (lcx, gy, gz); split form ((c - lcx) L + off)
         // in x and (dy L + off) in y, z; FP64 form (x - corner) in FP64, rounded
@@ -581,26 +811,33 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
         // predicate itself, on the exact, odd d.
         uint32_t ext[8];
         float lo[3], hi[3], fo[3];   // the box of the group's targets, and the lane's target of the test
-        double corner[3] = {0.0, 0.0, 0.0};
+        double corner[3] = {0.0, 0.0, 0.0}, ocorner[3] = {0.0, 0.0, 0.0};   // of the group, of the lane's target's group
         if constexpr (!SPLIT) {
             corner[0] = uniform_double(g.o[0] + (double)lcx * g.L);
             corner[1] = uniform_double(g.o[1] + (double)gy * g.L);
             corner[2] = uniform_double(g.o[2] + (double)gz * g.L);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) ocorner[d] = corner[d];
+            if (multi) {
+                ocorner[0] = g.o[0] + (double)ocx * g.L;
+                ocorner[1] = g.o[1] + (double)__shfl(wgy, 16 * og, kWave) * g.L;
+                ocorner[2] = g.o[2] + (double)__shfl(wgz, 16 * og, kWave) * g.L;
+                if (lane < 3) corner_of[gs][lane] = lane == 0 ? corner[0] : (lane == 1 ? corner[1] : corner[2]);
+            }
         }
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             float at;
             if constexpr (SPLIT)
-                at = d == 0 ? (real)(tcx - lcx) * T.Lf + tg.off[d][ti] : tg.off[d][ti];
+                at = d == 0 ? (real)(tcx - ocx) * T.Lf + tpos[d] : tpos[d];
             else
-                at = (float)(tg.x[d][ti] - corner[d]);
+                at = (float)(tpos[d] - ocorner[d]);
             const uint32_t o = ordered(at);
             ext[2 * d] = tin ? o : 0u;
             ext[2 * d + 1] = tin ? ~o : 0u;
             fo[d] = __shfl(at, lf, kWave);
         }
-        ext[6] = tin ? (uint32_t)tcx : 0u;
-        ext[7] = tin ? ~(uint32_t)tcx : 0u;
+        ext[6] = ext[7] = 0u;
         wave_max4(ext);
         wave_max4(ext + 4);
 #pragma unroll
@@ -608,12 +845,13 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
             hi[d] = unordered(ext[2 * d]);
             lo[d] = unordered(~ext[2 * d + 1]);
         }
-        const int gx1 = (int)ext[6], gx0 = (int)~ext[7];   // the targets' buckets
         const float f2 = fo[0] * fo[0] + fo[1] * fo[1] + fo[2] * fo[2];
-        const float fl = __builtin_amdgcn_sqrtf(f2) + A.h2;
+        const float fl = __builtin_amdgcn_sqrtf(f2) + at_round->A.h2;
         float margin = 0x1p-16f * fl * fl;
         if constexpr (!SPLIT) {
-            const float X = (float)(fabs(corner[0]) + fabs(corner[1]) + fabs(corner[2])) + fl;
+            float X = (float)(fabs(ocorner[0]) + fabs(ocorner[1]) + fabs(ocorner[2]));
+            if (multi) X = __shfl(X, lf, kWave);
+            X += fl;
             margin += 0x1p-46f * X * fl;
         }
         // Sources within 2h of a target lie within 2h of the targets' box, up to
@@ -624,12 +862,13 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
             const float m = fmaxf(fabsf(lo[d]), fabsf(hi[d]));
             b2 += m * m;
         }
-        const float bl = __builtin_amdgcn_sqrtf(b2) + A.h2;
+        const float bl = __builtin_amdgcn_sqrtf(b2) + at_round->A.h2;
         float bmargin = 0x1p-16f * bl * bl;
         if constexpr (!SPLIT) {
             const float X = (float)(fabs(corner[0]) + fabs(corner[1]) + fabs(corner[2])) + bl;
             bmargin += 0x1p-46f * X * bl;
         }
+        R2 = at_round->A.R2;
         const float bbound = (float)R2 + bmargin;
         // the product starts at minus the bound: its sign bit is the answer
         const float c0 = fin ? -(((float)R2 - f2) + margin) : kFar;
@@ -637,32 +876,8 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
         // operand B: component lane / 16 of (-2 f, 1) of target lane % 16
         const float bop = quarter == 3 ? 1.0f : -2.0f * (quarter == 0 ? fo[0] : (quarter == 1 ? fo[1] : fo[2]));
 
-        // the window: row r < 9 holds entries [off, off + n) of it, entry u is
-        // source u + del (lane r of every wavefront keeps row r's off and del)
-        const int xa = gx0 > 0 ? gx0 - 1 : 0, xb = gx1 + 1 < g.nx ? gx1 + 1 : g.nx - 1;
-        uint32_t wub = 0, wn = 0;
-        {
-            const int rz = (lane * 11) >> 5, z = gz + rz - 1, y = gy + (lane - 3 * rz) - 1;
-            if (lane < 9 && z >= 0 && z < g.nz && y >= 0 && y < g.ny) {
-                const uint32_t row = (uint32_t)g.nx * ((uint32_t)y + (uint32_t)g.ny * (uint32_t)z);
-                wub = sstart[row + xa];
-                wn = sstart[row + xb + 1] - wub;
-            }
-        }
-        uint32_t woff = wn;   // sums over lanes 0 .. r of the first row of 16
-        woff += (uint32_t)dpp<0x111>(0, (int)woff);
-        woff += (uint32_t)dpp<0x112>(0, (int)woff);
-        woff += (uint32_t)dpp<0x114>(0, (int)woff);
-        woff += (uint32_t)dpp<0x118>(0, (int)woff);
-        const uint32_t total = __builtin_amdgcn_readlane(woff, 8);
-        woff -= wn;
-        const uint32_t wdel = wub - woff;
-        const uint32_t hash0 = key * (uint32_t)g.nx + (uint32_t)lcx;   // of bucket (lcx, gy, gz)
-        const int rz = (lane * 11) >> 5;
-        // hash of bucket lcx of row `lane` of the window
-        const uint32_t rhash = hash0 + (uint32_t)g.nx * ((uint32_t)(lane - 3 * rz - 1) + (uint32_t)g.ny * (uint32_t)(rz - 1));
         // a source's position in the frame of the candidate test
-        auto framed = [&](const real *q, real dcx, real ddy, real ddz) {
+        auto framed = [&](const real *q, real dcx, real ddy, real ddz, const double *corner) {
             f32x4 a;
             if constexpr (SPLIT) {
                 a.x = dcx * T.Lf + q[0];
@@ -677,61 +892,67 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
         };
         uint32_t off[9];   // of the rows, in scalar registers
 #pragma unroll
-        for (int r = 1; r < 9; ++r) off[r] = __builtin_amdgcn_readlane(woff, r);
-        for (uint32_t batch = 0; batch < total; batch += kBatch) {
+        for (int r = 1; r < 9; ++r) off[r] = __builtin_amdgcn_readlane(woff, 16 * gs + r);
+        for (uint32_t batch = 0; batch < all; batch += kBatch) {
             // The batch's sources that are near no target are culled before their
-            // records are read.  Each wavefront looks at every fourth piece of 64
-            // entries, several pieces in flight, and lists what it keeps.
-            const uint32_t bend = min(total - batch, (uint32_t)kBatch) + batch;
+            // records are read.  Each wavefront looks at its share of its group's
+            // entries, whole pieces of 64 of them, several pieces in flight, and
+            // lists what it keeps.
+            const CallArgs<real> at_cull = call_args<real>();
+            const uint32_t here = min(total - batch, (uint32_t)kBatch);
+            const uint32_t piece = ((nw == 4 ? (here + 3) / 4 : (nw == 3 ? (here + 2) / 3 : (nw == 2 ? (here + 1) / 2 : here))) +
+                                    (kWave - 1)) & ~(uint32_t)(kWave - 1);
+            const uint32_t from = min(iw * piece, here), len = min(piece, here - from);
+            const uint32_t seg = place0 + from, bend = batch + from + len;
             uint32_t n = 0;
-            for (uint32_t w0 = batch + (uint32_t)(wave * kWave); w0 < bend; w0 += kAhead * kPairBlock) {
+            for (uint32_t w0 = batch + from; w0 < bend; w0 += kAhead * kWave) {
                 real q[kAhead][3];
                 uint32_t row[kAhead], hs[kAhead];
 #pragma unroll
                 for (int a = 0; a < kAhead; ++a) {
-                    const uint32_t u = min(w0 + (uint32_t)(a * kPairBlock + lane), bend - 1);
+                    const uint32_t u = min(w0 + (uint32_t)(a * kWave + lane), bend - 1);
                     int r = 0;
 #pragma unroll
                     for (int k = 1; k < 9; ++k) r += u >= off[k] ? 1 : 0;
-                    const uint32_t j = u + __shfl(wdel, r, kWave);
+                    const uint32_t j = u + __shfl(wdel, 16 * gs + r, kWave);
                     row[a] = r;
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) q[a][d] = SPLIT ? field(src.off[d], j) : (real)field(src.x[d], j);
-                    if constexpr (SPLIT) hs[a] = field(src.hash, j);
+                    for (int d = 0; d < 3; ++d) q[a][d] = SPLIT ? field(at_cull->src.off[d], j) : (real)field(at_cull->src.x[d], j);
+                    if constexpr (SPLIT) hs[a] = field(at_cull->src.hash, j);
                 }
 #pragma unroll
                 for (int a = 0; a < kAhead; ++a) {
-                    if (a && w0 + a * kPairBlock >= bend) break;
+                    if (a && w0 + a * kWave >= bend) break;
                     real dcx = 0, ddy = 0, ddz = 0;
                     if constexpr (SPLIT) {
-                        dcx = (real)(int)(hs[a] - __shfl(rhash, row[a], kWave));
+                        dcx = (real)(int)(hs[a] - __shfl(rhash, 16 * gs + (int)row[a], kWave));
                         const int z = (int)(row[a] * 11) >> 5;
                         ddy = (real)((int)row[a] - 3 * z - 1) * T.Lf;
                         ddz = (real)(z - 1) * T.Lf;
                     }
-                    const f32x4 at = framed(q[a], dcx, ddy, ddz);
+                    const f32x4 at = framed(q[a], dcx, ddy, ddz, corner);
                     // distances from the box along each axis
                     const float ex = fmaxf(fmaxf(lo[0] - at.x, at.x - hi[0]), 0.0f);
                     const float ey = fmaxf(fmaxf(lo[1] - at.y, at.y - hi[1]), 0.0f);
                     const float ez = fmaxf(fmaxf(lo[2] - at.z, at.z - hi[2]), 0.0f);
-                    const uint32_t u = w0 + (uint32_t)(a * kPairBlock + lane);
+                    const uint32_t u = w0 + (uint32_t)(a * kWave + lane);
                     const bool keep = u < bend && !(ex * ex + ey * ey + ez * ez > bbound);
-                    const uint64_t mask = __ballot(keep);
+                    const uint64_t mask = ballot(keep);
                     const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                    if (keep) kept_of[(uint32_t)(wave * kSeg) + n + rank] = (uint16_t)(row[a] << kEntryBits | (u - batch));
+                    if (keep) kept_of[seg + n + rank] = (uint16_t)(row[a] << kEntryBits | (u - batch));
                     n += (uint32_t)__popcll(mask);
                 }
             }
-            if (lane == 0) kept_n[wave] = n;
+            if (lane == 0) kept_n[wave] = n | len << 16;
             __syncthreads();   // the kept entries are listed, and every read of the page before is done
             uint32_t kept = 0, seg0[kPairWaves], jump[kPairWaves];
 #pragma unroll
             for (int w = 0; w < kPairWaves; ++w) {
-                const uint32_t n = __builtin_amdgcn_readfirstlane(kept_n[w]);
+                const uint32_t c = __builtin_amdgcn_readfirstlane(kept_n[w]), n = c & 0xFFFFu;
                 seg0[w] = kept;
                 kept += n;
-                jump[w] = (uint32_t)kSeg - n;   // from the end of the segment to the next one
+                jump[w] = (c >> 16) - n;   // from the end of the segment to the next one
             }
             // page p takes the kept entries p, p + npages, ..., so that every page
             // holds an even share of each target's hits
@@ -749,34 +970,42 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
                 // Blocks need not end where 64 lanes do: what lies past the last
                 // one has no place.
                 const uint32_t ends = blocks * (4 * kRows);
+                const CallArgs<real> at_load = call_args<real>();
 #pragma unroll 1
                 for (uint32_t w0 = (uint32_t)(wave * kWave); w0 < ends; w0 += kPairBlock) {
                     const uint32_t u = w0 + (uint32_t)lane;
                     const uint32_t v = min(u, len - 1) * npages + page;   // of the kept entries
-                    uint32_t at = v;
+                    uint32_t at = v, sv = 0;   // its place, and its segment
 #pragma unroll
-                    for (int w = 1; w < kPairWaves; ++w) at += v >= seg0[w] ? jump[w - 1] : 0u;
+                    for (int w = 1; w < kPairWaves; ++w) {
+                        at += v >= seg0[w] ? jump[w - 1] : 0u;
+                        sv += v >= seg0[w] ? 1u : 0u;
+                    }
                     const uint32_t code = kept_of[at];
-                    const int r = (int)(code >> kEntryBits);
-                    const uint32_t j = batch + (code & ((1u << kEntryBits) - 1u)) + __shfl(wdel, r, kWave);
-                    const uint32_t hr = SPLIT ? __shfl(rhash, r, kWave) : 0u;
+                    const uint32_t gv = gm >> (2 * sv) & 3u;   // its group
+                    const int r = (int)(code >> kEntryBits), wl = (int)gv * 16 + r;
+                    const uint32_t j = batch + (code & ((1u << kEntryBits) - 1u)) + __shfl(wdel, wl, kWave);
+                    const uint32_t hr = SPLIT ? __shfl(rhash, wl, kWave) : 0u;
                     const uint32_t place = u / (uint32_t)kRows, row = u % (uint32_t)kRows;
                     f32x4 a = {0.0f, 0.0f, 0.0f, kFar};   // past the page's end: no target takes it
                     if (u < len) {
                         real q[W::NR];
                         if constexpr (SPLIT) {
 #pragma unroll
-                            for (int d = 0; d < 3; ++d) q[d] = field(src.off[d], j);
-                            q[3] = (real)(int)(field(src.hash, j) - hr);
+                            for (int d = 0; d < 3; ++d) q[d] = field(at_load->src.off[d], j);
+                            q[3] = (real)(int)(field(at_load->src.hash, j) - hr);
                             const int z = (r * 11) >> 5;
                             q[W::NR - 2] = (real)(r - 3 * z - 1) * T.Lf;
                             q[W::NR - 1] = (real)(z - 1) * T.Lf;
                         } else {
 #pragma unroll
-                            for (int d = 0; d < 3; ++d) q[d] = field(src.x[d], j);
+                            for (int d = 0; d < 3; ++d) q[d] = field(at_load->src.x[d], j);
                         }
-                        load_fields<real, PASS, SOLID>(src, Rsrc, cz, j, q + W::NPOS);
-                        a = framed(q, q[3], q[W::NR - 2], q[W::NR - 1]);
+                        load_fields<real, PASS, SOLID>(at_load, j, q + W::NPOS);
+                        if (SPLIT || !multi)
+                            a = framed(q, q[3], q[W::NR - 2], q[W::NR - 1], corner);
+                        else
+                            a = framed(q, 0, 0, 0, corner_of[gv]);
                         a.w = a.x * a.x + a.y * a.y + a.z * a.z;
                         const uint32_t k = row * (uint32_t)kPitch + place;
 #pragma unroll
@@ -827,10 +1056,17 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
                 }
                 __syncthreads();   // every read of the operands is done: the lists take their place
                 if (!in_tile) continue;
+                const uint32_t top = 4 * blocks - 1;   // place 0's bit
+                {
+                    const CallArgs<real> at_eval = call_args<real>();
+                    K.hinv = at_eval->A.K.hinv, K.Fc = at_eval->A.K.Fc, K.beta = at_eval->A.K.beta;
+                    K.half_beta = at_eval->A.K.half_beta, K.F3 = at_eval->A.K.F3, K.F225 = at_eval->A.K.F225;
+                    K.F075 = at_eval->A.K.F075, K.hb4 = at_eval->A.K.hb4, K.hbq = at_eval->A.K.hbq;
+                    R2 = at_eval->A.R2;
+                }
                 int own = 0;
 #pragma unroll
                 for (int k = 0; k < kWords; ++k) own += __popc(word[k]);
-                const uint32_t top = 4 * blocks - 1;   // place 0's bit
                 // the four lanes that tested a target list its hits one after the other
                 const int own16 = __shfl_xor(own, 16, kWave);
                 const int two = own + own16, two32 = __shfl_xor(two, 32, kWave);
@@ -839,8 +1075,8 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
                 const int mine = __shfl(all, lane / kShare, kWave);   // of the target the lane evaluates
                 // rounds of up to kCap listed hits per target (one, unless the
                 // particles are far denser than a lattice)
-                const bool fits = !__ballot(all > kCap);
-                for (int done = 0; __ballot(all > done); done += kCap) {
+                const bool fits = !ballot(all > kCap);
+                for (int done = 0; ballot(all > done); done += kCap) {
                     uint16_t *to = list + lf * kListPitch;
                     int pos = before - done;
 #pragma unroll
@@ -916,8 +1152,8 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
             scen += __shfl_xor(scen, off, kWave);
         }
         if (valid && sub == 0) {
-            cz.count[i] = ncen;
-            cz.sum[i] = scen;
+            call.cz.count[i] = ncen;
+            call.cz.sum[i] = scen;
         }
     } else {
         // The workgroup's sums go through LDS, so that a wavefront reads and
@@ -934,22 +1170,25 @@ void k_pairs(PairArgs<real> A, Grid g, PV<real> tg, const uint32_t *__restrict__
         }
         __syncthreads();
         if (!tvalid) return;
+        const CallArgs<real> at_end = call_args<real>();
+        const auto &B = at_end->B;
         real *const adj[17] = {B.x[0], B.x[1], B.x[2], B.v[0], B.v[1], B.v[2], B.w, B.rho, B.p, B.c, B.e,
                                B.S[0], B.S[1], B.S[2], B.S[3], B.S[4], B.S[5]};
 #pragma unroll
         for (int k = 0; k < NOUT; ++k) {
-            if ((k & (kPairWaves - 1)) != wave) continue;
+            if ((k & (kPairWaves - 1)) != wave0) continue;
             double sum = sums[k * kGroup + lane];
             if constexpr (ADJ || GADJ) {
                 // accumulate the cotangents of x, v, omega (FORCE: rho, p, c, e and S too)
-                adj[k][ti] = (real)((double)adj[k][ti] + sum);
+                auto &to = entry(adj[k], ti);
+                to = (real)((double)to + sum);
             } else {
-                real *hi = FORCE ? R.hi[k] : R.Lhi[k];
-                real *lo = FORCE ? R.lo[k] : R.Llo[k];
-                if (!zero_first) sum += SPLIT ? (double)hi[ti] + (double)lo[ti] : (double)hi[ti];
+                auto &hi = entry(FORCE ? at_end->R.hi[k] : at_end->R.Lhi[k], ti);
+                auto &lo = entry(SPLIT ? (FORCE ? at_end->R.lo[k] : at_end->R.Llo[k]) : (real *)nullptr, SPLIT ? ti : 0u);
+                if (!at_end->zero_first) sum += SPLIT ? (double)hi + (double)lo : (double)hi;
                 const real hv = (real)sum;
-                hi[ti] = hv;
-                if (SPLIT) lo[ti] = (real)(sum - (double)hv);
+                hi = hv;
+                if constexpr (SPLIT) lo = (real)(sum - (double)hv);
             }
         }
     }
@@ -1047,12 +1286,12 @@ hipError_t go(const Params &P, const Grid &g, const sph_particles &tg, const uin
         const hipError_t e = hipEventRecord(ev_begin, s);
         if (e != hipSuccess) return e;
     }
-    const PairArgs<real> A{make_pair_k<real>(P), (real)P.R2, (float)(2.0 * P.h)};
-    auto launch = [&](auto kernel, int group) {
-        kernel<<<div_up(tg.n, group), kPairBlock, 0, s>>>(A, g, view<real>(tg), tidx, nt, view<real>(sr), sstart, zero_first,
-                                                          view<real>(r), view<real>(rsrc ? *rsrc : none), view<real>(bar),
-                                                          cz);
-    };
+    const real linv = g.L > 0x1p-60 && g.L < 0x1p45 ? (real)(1.0 / g.L) : (real)NAN;
+    auto above = [](int d) { return (1.0 + 0x1p-50) / d; };
+    const PairCall<real> call{{make_pair_k<real>(P), (real)P.R2, (float)(2.0 * P.h)}, g, view<real>(tg), tidx, nt,
+                              view<real>(sr), sstart, above(g.nx), above(g.ny), linv, zero_first, view<real>(r), view<real>(rsrc ? *rsrc : none),
+                              view<real>(bar), cz};
+    auto launch = [&](auto kernel, int group) { kernel<<<div_up(tg.n, group), kPairBlock, 0, s>>>(call); };
     // The fewest targets per wavefront whose workgroups are all resident at
     // once (one per SIMD's wavefront on each CU): below that a call is bound by
     // the latency of one workgroup's chain of loads, barriers and bucket rows,

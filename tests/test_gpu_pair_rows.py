@@ -1,0 +1,122 @@
+"""The pair kernel where bucket rows hold few targets, so that a workgroup's
+targets lie in several rows whose windows it takes together: gases of 0.05 to
+4 particles a bucket, few and many rows, rows whose ends lie at the same place
+(which must not see each other's sources), particles beyond the grid, and
+target lists in any order.
+
+Neighbour sets are compared exactly (tests/census.py), the FORCE sums of one
+gas of each kind with the oracle, within the round-off bounds of
+tests/gpu_helpers.py."""
+import numpy as np
+import pytest
+import torch
+
+import sph_synth as S
+from oracle import cpu
+from tests.gpu_helpers import assert_within, oracle_state, rate_bound
+from tests.test_gpu_census import check_census
+
+pytestmark = pytest.mark.gpu
+
+PRECS = [pytest.param(0, id="fp64"), pytest.param(1, id="fp32split")]
+SIDE = 0.125   # of a bucket
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _gas(n, dims, seed, kind="even", origin=(0.0, 0.0, 0.0), material=None):
+    wl = (S.random_cloud(n, seed=seed, h=SIDE / 2) if material is None
+          else S.solid_block(round(n ** (1 / 3)), seed=seed, s_sigma=1e7))
+    n = wl.n
+    rng = np.random.default_rng(seed)
+    u = rng.random((n, 3))
+    if kind == "ends":   # at the two ends of every row, in the same places of their buckets
+        u[:, 0] = np.where(rng.random(n) < 0.5, 0.3 + 0.4 * u[:, 0], dims[0] - 0.7 + 0.4 * u[:, 0]) / dims[0]
+        u[:, 1:] = (np.floor(u[:, 1:] * dims[1:]) + 0.45 + 0.1 * rng.random((n, 2))) / dims[1:]
+    if kind == "beyond":   # one in 20 outside the grid, by up to 4 buckets
+        out = rng.random(n) < 0.05
+        u[out] += rng.uniform(-4.0, 4.0, (out.sum(), 3)) / dims
+    wl.grid = dict(wl.grid, origin=list(origin), cell=SIDE, dims=list(dims))
+    wl.params = dict(wl.params, h=SIDE / 2)
+    wl.x = np.asarray(origin) + u * np.asarray(dims) * SIDE
+    return wl
+
+
+# (particles, buckets): each width of the kernel; 0.05, 0.5, 2 and 4 a bucket; many short rows and a few long ones
+GASES = [(300, (20, 20, 15)), (5000, (10, 40, 25)), (5000, (700, 3, 3)), (20000, (40, 50, 20)), (20000, (6, 80, 84)),
+         (40000, (70, 50, 23)), (40000, (30, 18, 19)), (40000, (5000, 4, 4))]
+
+
+def _check(sim, what, prec):
+    cnt, chk = sim.census()
+    h = sim.A.host()
+    t = np.arange(sim.n) if sim.n <= 5000 else np.unique(np.random.default_rng(1).integers(0, sim.n, 3000))
+    check_census(cnt, chk, t, h["x"][t], h["x"], h["id"], SIDE / 2, prec, what)
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("kind", ["even", "ends", "beyond"])
+@pytest.mark.parametrize("n,dims", GASES)
+def test_neighbour_sets_of_a_gas(n, dims, kind, prec):
+    from paper_2310_03596_amd.sim import Sim
+    print(f"[rows] n={n} dims={dims} {kind} prec={prec}", flush=True)
+    sim = Sim(_gas(n, dims, 780 + n, kind), prec)
+    sim.build()
+    _check(sim, f"{n} in {dims}, {kind}", prec)
+
+
+@pytest.mark.parametrize("origin", [1e3, 1e11])   # the second past where rows are taken together in FP64
+def test_a_grid_far_from_the_origin(origin):
+    from paper_2310_03596_amd.sim import Sim
+    print(f"[rows] origin={origin}", flush=True)
+    sim = Sim(_gas(5000, (10, 40, 25), 781, "ends", (origin, -origin, origin)), 0)
+    sim.build()
+    _check(sim, f"origin {origin}", 0)
+
+
+@pytest.mark.parametrize("prec", PRECS)
+def test_a_list_in_any_order(prec):
+    from paper_2310_03596_amd import _lib as L
+    from paper_2310_03596_amd.sim import Sim
+    from paper_2310_03596_amd.state import stream_handle
+    sim = Sim(_gas(5000, (30, 16, 10), 782), prec)
+    sim.build()
+    pick = np.random.default_rng(783).permutation(sim.n)[:3001]
+    print(f"[rows] list prec={prec}", flush=True)
+    dev = sim.A.x.device
+    tidx = torch.from_numpy(pick.astype(np.int32)).to(dev)
+    nt = torch.tensor([pick.size], dtype=torch.int32, device=dev)
+    cnt = torch.zeros(sim.n, dtype=torch.int32, device=dev)
+    chk = torch.zeros(sim.n, dtype=torch.int64, device=dev)
+    a = sim.A.struct()
+    L.sph_neighbor_census(sim.params, sim.grid, L.SPH_PASS_FORCE, a, tidx.data_ptr(), nt.data_ptr(), a, sim.cells,
+                          cnt.data_ptr(), chk.data_ptr(), sim.ws.data_ptr(), sim.ws_bytes, stream_handle())
+    torch.cuda.synchronize()
+    h = sim.A.host()
+    c, k = cnt.cpu().numpy().view(np.uint32), chk.cpu().numpy().view(np.uint64)
+    check_census(c, k, pick, h["x"][pick], h["x"], h["id"], SIDE / 2, prec, "list")
+    off = np.setdiff1d(np.arange(sim.n), pick)
+    assert not c[off].any() and not k[off].any()
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("solid", [False, True], ids=["fluid", "solid"])
+@pytest.mark.parametrize("kind,dims", [("even", (12, 20, 20)), ("ends", (40, 20, 20))])
+def test_force_of_a_gas_matches_oracle(kind, dims, solid, prec):
+    from paper_2310_03596_amd.sim import Sim
+    print(f"[rows] force {kind} solid={solid} prec={prec}", flush=True)
+    sim = Sim(_gas(4096, dims, 784, kind, material="solid" if solid else None), prec)
+    sim.build()
+    for pass_ in (0, 1) if solid else (0,):
+        sim.interact(pass_=pass_)
+        torch.cuda.synchronize()
+        st = oracle_state(sim.A.host(), solid)
+        start = cpu.cell_start(st.hash, cpu.ncells(sim.wl.grid))
+        ref = cpu.interact(sim.wl.params, sim.wl.grid, pass_, st, st, start, True)
+        bound = rate_bound(sim.wl.params, sim.wl.grid, pass_, st, st, start, True, prec)
+        got = sim.rates.grad() if pass_ else sim.rates.force()
+        assert_within(got.T.cpu().numpy(), ref, bound, f"gas pass {pass_}")
