@@ -333,7 +333,7 @@ int sph_neighbor_census(const sph_params *params, const sph_grid *grid, int pass
     bool self = targets->hash == sources->hash;
     if (self && targets->n != sources->n)
         return fail(SPH_ERR_ARG, "targets and sources share their hash array but not their size");
-    return hip_status(launch_census(P, g, params->prec, *targets, target_idx, n_targets_dev, *sources,
+    return hip_status(launch_census(P, g, params->prec, pass, *targets, target_idx, n_targets_dev, *sources,
                                     source_cells.start, count_out, checksum_out, (hipStream_t)stream),
                       "sph_neighbor_census");
 }

@@ -89,7 +89,6 @@ constexpr int kEntryBits = 11;                    // of a kept entry's code: its
 static_assert(kBatch <= 1 << kEntryBits, "a batch's entries");
 constexpr int kPassAdjoint = 2;            // reverse mode of the FORCE pass
 constexpr int kPassGradAdjoint = 4;        // reverse mode of the GRADIENT pass
-constexpr int kPassCensus = 3;             // neighbour census of a FORCE or GRADIENT pass
 
 // Census outputs: per target, the number of sources the pass evaluates
 // (r^2 < (2h)^2 on the rebuilt d, the pairs at r = 0 included) and the sum,
@@ -122,11 +121,11 @@ struct Pass {
     static constexpr int kShare = kWave / TILE;        // lanes that share a target
     static_assert(TILE <= 16 && kGroup <= kWave, "lane l of every wavefront looks at target l of the workgroup");
     static constexpr bool SPLIT = sizeof(real) == 4;
-    static constexpr bool ADJ = PASS == kPassAdjoint, GADJ = PASS == kPassGradAdjoint, CENSUS = PASS == kPassCensus;
+    static constexpr bool ADJ = PASS == kPassAdjoint, GADJ = PASS == kPassGradAdjoint;
     static constexpr bool FORCE = PASS == SPH_PASS_FORCE, GRAD = PASS == SPH_PASS_GRADIENT;
-    static constexpr int NOUT = FORCE ? 6 : (ADJ ? (SOLID ? 17 : 11) : (GADJ ? 7 : (CENSUS ? 1 : 9)));
+    static constexpr int NOUT = FORCE ? 6 : (ADJ ? (SOLID ? 17 : 11) : (GADJ ? 7 : 9));
     static constexpr int NPOS = SPLIT ? 4 : 3;
-    static constexpr int NF = FORCE ? (SOLID ? 14 : 8) : (ADJ ? (SOLID ? 20 : 14) : (GADJ ? 13 : (CENSUS ? 1 : 4)));
+    static constexpr int NF = FORCE ? (SOLID ? 14 : 8) : (ADJ ? (SOLID ? 20 : 14) : (GADJ ? 13 : 4));
     static constexpr int NR = NPOS + NF + (SPLIT ? 2 : 0);   // reals of a record
     static constexpr int C = 16 / (int)sizeof(real);          // reals per 16 bytes
     static constexpr int REST = NR % C;
@@ -401,11 +400,13 @@ __device__ inline __attribute__((address_space(1))) T &entry(T *base, uint32_t j
 }
 
 // The fields of source j that a pass reads, in record order.
-template <typename real, int PASS, bool SOLID>
+template <typename real, int PASS, bool SOLID, bool CENSUS>
 __device__ inline void load_fields(CallArgs<real> a, uint32_t j, real *f)
 {
     using W = Pass<real, PASS, SOLID>;
-    if constexpr (W::CENSUS) {
+    if constexpr (CENSUS) {   // the id in place of the first
+#pragma unroll
+        for (int k = 1; k < W::NF; ++k) f[k] = real(0);
         if constexpr (W::SPLIT)
             f[0] = __builtin_bit_cast(float, field(a->cz.sid, j));
         else
@@ -436,13 +437,15 @@ __device__ inline void load_fields(CallArgs<real> a, uint32_t j, real *f)
     }
 }
 
-template <typename real, int PASS, bool SOLID, int TILE>
+// (CENSUS: the pass's neighbour sets instead of its sums, by the same pages,
+// lists and launches.)
+template <typename real, int PASS, bool SOLID, int TILE, bool CENSUS>
 __global__ __launch_bounds__(kPairBlock)
 __attribute__((amdgpu_waves_per_eu(Pass<real, PASS, SOLID, TILE>::waves)))
 void k_pairs(PairCall<real> call)
 {
     using W = Pass<real, PASS, SOLID, TILE>;
-    constexpr bool SPLIT = W::SPLIT, ADJ = W::ADJ, GADJ = W::GADJ, CENSUS = W::CENSUS, FORCE = W::FORCE;
+    constexpr bool SPLIT = W::SPLIT, ADJ = W::ADJ, GADJ = W::GADJ, FORCE = W::FORCE;
     constexpr int NOUT = W::NOUT, kPage = W::kPage, kCap = W::kCap, C = W::C;
     constexpr int kGroup = W::kGroup, kShare = W::kShare;
     constexpr int kRows = W::kRows, kPitch = W::kPitch, kCandPitch = W::kCandPitch;
@@ -519,9 +522,10 @@ void k_pairs(PairCall<real> call)
     }
     Part<real, SOLID> I;
     real rbi[GADJ ? 9 : 6];   // adjoint: the target's rate (or velocity-gradient) cotangents
-    if constexpr (FORCE || ADJ) {
+    if constexpr (CENSUS) {
+    } else if constexpr (FORCE || ADJ) {
         load_part<real, SOLID>(tg, i, I);
-    } else if constexpr (!CENSUS) {
+    } else {
 #pragma unroll
         for (int d = 0; d < 3; ++d) I.v[d] = tg.v[d][i];
         if constexpr (GADJ) I.w = tg.w[i];
@@ -1001,7 +1005,7 @@ void k_pairs(PairCall<real> call)
 #pragma unroll
                             for (int d = 0; d < 3; ++d) q[d] = field(at_load->src.x[d], j);
                         }
-                        load_fields<real, PASS, SOLID>(at_load, j, q + W::NPOS);
+                        load_fields<real, PASS, SOLID, CENSUS>(at_load, j, q + W::NPOS);
                         if (SPLIT || !multi)
                             a = framed(q, q[3], q[W::NR - 2], q[W::NR - 1], corner);
                         else
@@ -1270,9 +1274,8 @@ __global__ __launch_bounds__(kBlock) void k_count(Params P, Grid g, PV<real> tg,
     }
 }
 
-// One pass.  The census (PASS = kPassCensus) runs the window, candidate test
-// and lists of the other passes.
-template <typename real, int PASS, bool SOLID>
+// One pass, or its census.
+template <typename real, int PASS, bool SOLID, bool CENSUS = false>
 hipError_t go(const Params &P, const Grid &g, const sph_particles &tg, const uint32_t *tidx,
               const uint32_t *nt, const sph_particles &sr, const uint32_t *sstart, int zero_first,
               const sph_rates &r, const sph_adjoint &bar, hipStream_t s, const Census cz = Census{},
@@ -1303,11 +1306,11 @@ hipError_t go(const Params &P, const Grid &g, const sph_particles &tg, const uin
     using W4 = Pass<real, PASS, SOLID, 4>;
     using W8 = Pass<real, PASS, SOLID, 8>;
     if (div_up(tg.n, W4::kGroup) <= kCUs * W4::waves)
-        launch(k_pairs<real, PASS, SOLID, 4>, W4::kGroup);
+        launch(k_pairs<real, PASS, SOLID, 4, CENSUS>, W4::kGroup);
     else if (div_up(tg.n, W8::kGroup) <= kCUs * W8::waves)
-        launch(k_pairs<real, PASS, SOLID, 8>, W8::kGroup);
+        launch(k_pairs<real, PASS, SOLID, 8, CENSUS>, W8::kGroup);
     else
-        launch(k_pairs<real, PASS, SOLID, 16>, Pass<real, PASS, SOLID, 16>::kGroup);
+        launch(k_pairs<real, PASS, SOLID, 16, CENSUS>, Pass<real, PASS, SOLID, 16>::kGroup);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return le;
     if (ev_begin && ev_end) return hipEventRecord(ev_end, s);
@@ -1366,15 +1369,22 @@ hipError_t launch_count_pairs(const Params &P, const Grid &g, int prec, const sp
     return hipGetLastError();
 }
 
-hipError_t launch_census(const Params &P, const Grid &g, int prec, const sph_particles &tg, const uint32_t *tidx,
-                         const uint32_t *nt, const sph_particles &sr, const uint32_t *sstart, uint32_t *count,
-                         uint64_t *sum, hipStream_t s)
+hipError_t launch_census(const Params &P, const Grid &g, int prec, int pass, const sph_particles &tg,
+                         const uint32_t *tidx, const uint32_t *nt, const sph_particles &sr, const uint32_t *sstart,
+                         uint32_t *count, uint64_t *sum, hipStream_t s)
 {
     const sph_rates none{};
     const sph_adjoint nobar{};
     const Census cz{count, reinterpret_cast<unsigned long long *>(sum), sr.id};
-    if (prec == SPH_FP64) return go<double, kPassCensus, false>(P, g, tg, tidx, nt, sr, sstart, 1, none, nobar, s, cz);
-    return go<float, kPassCensus, false>(P, g, tg, tidx, nt, sr, sstart, 1, none, nobar, s, cz);
+    auto run = [&](auto real_v) {
+        using real = decltype(real_v);
+        if (pass == SPH_PASS_GRADIENT)
+            return go<real, SPH_PASS_GRADIENT, false, true>(P, g, tg, tidx, nt, sr, sstart, 1, none, nobar, s, cz);
+        if (P.material == SPH_SOLID_J2)
+            return go<real, SPH_PASS_FORCE, true, true>(P, g, tg, tidx, nt, sr, sstart, 1, none, nobar, s, cz);
+        return go<real, SPH_PASS_FORCE, false, true>(P, g, tg, tidx, nt, sr, sstart, 1, none, nobar, s, cz);
+    };
+    return prec == SPH_FP64 ? run(double()) : run(float());
 }
 
 hipError_t launch_interact_adjoint(const Params &P, const Grid &g, int prec, int pass, const sph_particles &tg,
