@@ -15,6 +15,7 @@ import sph_synth as S
 from oracle import cpu
 from tests.gpu_helpers import assert_within, oracle_state, rate_bound
 from tests.test_gpu_census import check_census
+from tests.test_gpu_pair_dense import _reverse
 
 pytestmark = pytest.mark.gpu
 
@@ -120,3 +121,28 @@ def test_force_of_a_gas_matches_oracle(kind, dims, solid, prec):
         bound = rate_bound(sim.wl.params, sim.wl.grid, pass_, st, st, start, True, prec)
         got = sim.rates.grad() if pass_ else sim.rates.force()
         assert_within(got.T.cpu().numpy(), ref, bound, f"gas pass {pass_}")
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("solid,pass_", [(False, 0), (True, 0), (True, 1)], ids=["fluid", "solid", "gradient"])
+def test_reverse_of_a_gas(solid, pass_, prec):
+    """Against the pair terms differentiated by torch, with the bound of tests/test_gpu_pair_dense.py."""
+    from paper_2310_03596_amd import _lib as L
+    from paper_2310_03596_amd.adjoint import Cotangent
+    from paper_2310_03596_amd.sim import Sim
+    from paper_2310_03596_amd.state import Rates, stream_handle
+    print(f"[rows] reverse solid={solid} pass={pass_} prec={prec}", flush=True)
+    sim = Sim(_gas(4096, (12, 20, 20), 785, material="solid" if solid else None), prec)
+    sim.build()
+    rbar, bar = Rates(sim.n, prec, solid, "cuda"), Cotangent(sim.n, prec, "cuda", solid)
+    to = rbar.Lhi if pass_ else rbar.hi
+    to.copy_(torch.from_numpy(np.random.default_rng(786).normal(size=to.shape)))
+    a, r = sim.A.struct(), rbar.struct()
+    wsb = L.sph_workspace_size(sim.grid, sim.n, prec, L.SPH_SOLID_J2)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    L.sph_interact_adjoint(sim.params, sim.grid, pass_, a, None, None, a, sim.cells, r, r, bar.struct(), ws.data_ptr(),
+                           wsb, stream_handle())
+    want = _reverse(sim.wl, sim.A.host(), pass_, to.double().T.cpu(), np.arange(sim.n), solid)
+    for f, (ref, size) in want.items():
+        got = getattr(bar, f).double().reshape(-1, sim.n).T.cpu().numpy()
+        assert np.abs(got - ref).max() <= 1e4 * (2.0 ** -24 if prec else 2.0 ** -53) * size.max(), f
