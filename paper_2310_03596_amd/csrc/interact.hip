@@ -514,12 +514,10 @@ void k_pairs(PairCall<real> call)
         }
     }
     // Listed targets need not ascend; where they do, a group's outer buckets are
-    // those of its first and last target.
-    bool ascend = true;
-    if (listed) {
-        const uint32_t before = __shfl_up(th, 1, kWave);
-        ascend = !ballot(lane > 0 && tvalid && th < before);
-    }
+    // those of its first and last target.  (All lanes' hashes are looked at, those of
+    // indices outside the array too: no descent can hide behind one.)
+    const uint32_t before = __shfl_up(th, 1, kWave);
+    const bool ascend = !ballot(lane > 0 && lane < kGroup && t < nt && th < before);
     Part<real, SOLID> I;
     real rbi[GADJ ? 9 : 6];   // adjoint: the target's rate (or velocity-gradient) cotangents
     if constexpr (CENSUS) {

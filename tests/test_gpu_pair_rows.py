@@ -105,6 +105,57 @@ def test_a_list_in_any_order(prec):
 
 
 @pytest.mark.parametrize("prec", PRECS)
+def test_a_list_that_only_seems_to_ascend(prec):
+    """Targets of a row in descending order, with an index outside the array between any two."""
+    from paper_2310_03596_amd import _lib as L
+    from paper_2310_03596_amd.sim import Sim
+    from paper_2310_03596_amd.state import stream_handle
+    sim = Sim(_gas(5000, (300, 4, 4), 787), prec)
+    sim.build()
+    pick = np.arange(sim.n)[::-1][:1000]
+    lst = np.full(2 * pick.size, sim.n, dtype=np.int32)
+    lst[::2] = pick
+    print(f"[rows] broken list prec={prec}", flush=True)
+    dev = sim.A.x.device
+    tidx = torch.from_numpy(lst).to(dev)
+    nt = torch.tensor([lst.size], dtype=torch.int32, device=dev)
+    cnt = torch.zeros(sim.n, dtype=torch.int32, device=dev)
+    chk = torch.zeros(sim.n, dtype=torch.int64, device=dev)
+    a = sim.A.struct()
+    L.sph_neighbor_census(sim.params, sim.grid, L.SPH_PASS_FORCE, a, tidx.data_ptr(), nt.data_ptr(), a, sim.cells,
+                          cnt.data_ptr(), chk.data_ptr(), sim.ws.data_ptr(), sim.ws_bytes, stream_handle())
+    torch.cuda.synchronize()
+    h = sim.A.host()
+    c, k = cnt.cpu().numpy().view(np.uint32), chk.cpu().numpy().view(np.uint64)
+    check_census(c, k, pick, h["x"][pick], h["x"], h["id"], SIDE / 2, prec, "broken list")
+
+
+@pytest.mark.parametrize("prec", PRECS)
+def test_an_array_of_targets_in_any_order(prec):
+    """All targets of an array that is not sorted, over sources that are."""
+    from paper_2310_03596_amd import _lib as L
+    from paper_2310_03596_amd.sim import Sim
+    from paper_2310_03596_amd.state import stream_handle
+    sim = Sim(_gas(5000, (30, 16, 10), 788), prec)
+    sim.build()
+    print(f"[rows] unsorted targets prec={prec}", flush=True)
+    mixed = sim.A.clone()
+    order = torch.from_numpy(np.random.default_rng(789).permutation(sim.n)).cuda()
+    for f in ("x", "off", "hash", "id"):
+        t = getattr(mixed, f)
+        if t is not None:
+            t.copy_(t[..., order].clone())
+    cnt = torch.zeros(sim.n, dtype=torch.int32, device="cuda")
+    chk = torch.zeros(sim.n, dtype=torch.int64, device="cuda")
+    L.sph_neighbor_census(sim.params, sim.grid, L.SPH_PASS_FORCE, mixed.struct(), None, None, sim.A.struct(), sim.cells,
+                          cnt.data_ptr(), chk.data_ptr(), sim.ws.data_ptr(), sim.ws_bytes, stream_handle())
+    torch.cuda.synchronize()
+    t, h = mixed.host(), sim.A.host()
+    c, k = cnt.cpu().numpy().view(np.uint32), chk.cpu().numpy().view(np.uint64)
+    check_census(c, k, np.arange(sim.n), t["x"], h["x"], h["id"], SIDE / 2, prec, "unsorted targets")
+
+
+@pytest.mark.parametrize("prec", PRECS)
 @pytest.mark.parametrize("solid", [False, True], ids=["fluid", "solid"])
 @pytest.mark.parametrize("kind,dims", [("even", (12, 20, 20)), ("ends", (40, 20, 20))])
 def test_force_of_a_gas_matches_oracle(kind, dims, solid, prec):
