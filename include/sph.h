@@ -236,9 +236,12 @@ int sph_pack_boundary(const sph_particles *local, const uint32_t *boundary_idx,
  * (solids: Cauchy stress -p I + S); SPH_PASS_GRADIENT: velocity gradient L.
  * zero_first = 1 overwrites the rate entries of the targets, 0 adds to them
  * (the local-remote pass, step f, continues the sums of step e from hi + lo).
- * The order of summation over j (four sums per target, then added) depends on
- * the order of the particles alone, so repeated calls agree bit for bit.  Both
- * arrays must be hash-sorted on `grid`.  The workspace (sized by
+ * A target's sum is made of 4, 8 or 16 partial sums (by targets->n), whose
+ * terms and order depend on the positions and on which other targets are near
+ * it in the array or list.  Calls with the same arrays, counts and list agree
+ * bit for bit; the same target reached through another list, or through the
+ * whole array, may differ by the rounding of the FP64 sums.  Both arrays must
+ * be hash-sorted on `grid`.  The workspace (sized by
  * sph_workspace_size for sources->n) is checked and not written.
  * Errors: SPH_ERR_ARG (precision or material mismatch, missing field,
  * sources->n at or above 2^27 = 134,217,728), SPH_ERR_WORKSPACE. */
@@ -286,9 +289,10 @@ int sph_set_pair_events(void *begin_event, void *end_event);
 /* Neighbour census of one interaction pass (Section I: a particle's
  * neighbours lie in its own bucket or the 26 around it).  Takes the arguments
  * of sph_interact without the rates and runs the same wavefront mapping,
- * candidate test, hit lists and neighbour predicate as that pass would, but
- * instead of the pair terms it writes, for every target i, count_out[i] = the number of sources
- * j the pass evaluates (r_ij^2 < (2h)^2 on the position difference the pass
+ * pages, candidate test, hit lists and neighbour predicate as that pass would
+ * (pass and params->material choose which), but instead of the pair terms it
+ * writes, for every target i, count_out[i] = the number of sources j the pass
+ * evaluates (r_ij^2 < (2h)^2 on the position difference the pass
  * rebuilds; j == i and coincident particles, whose terms are exactly zero,
  * included) and checksum_out[i] = the sum modulo 2^64 of
  * splitmix64(sources->id[j]) over them, with

@@ -52,13 +52,21 @@
 // wait for the one with the most hits in a page (22 rounds of the body per
 // wavefront instead of 26; 20.25 if no lane ever waited).  Measured per pass,
 // reads from L1 with their staging kernel first, whole windows in LDS second,
-// culled ones third: column FORCE FP32 401, 391, 350 us, FP64 675, 572, 520;
-// 4.0 M cylinder (FP32) FORCE 2.89, 2.59, 2.23 ms, GRADIENT 1.62, 1.50, 1.31;
-// 6.7 M impact (FP64) FORCE 8.83, 6.53, 5.95 ms, GRADIENT 4.02, 3.04, 2.80;
-// 250,047-particle FORCE reverse FP32 260, 248, 233 us; 27,000 ones FP64 FORCE
-// 54, 43, 39 us; 8,000 ones FP32 63, 33, 28 us (17 with 16 targets per workgroup).  Culling and loading in one
-// sweep instead of two was slower (441 us for the column's 373): each
-// source's fields then wait for its position.
+// culled ones third, several rows together fourth: column FORCE FP32 401, 391,
+// 350, 330 us, FP64 675, 572, 520, 500; 4.0 M cylinder (FP32) FORCE 2.89, 2.59,
+// 2.23, 2.16 ms, GRADIENT 1.62, 1.50, 1.31, 1.31; 6.7 M impact (FP64) FORCE 8.83,
+// 6.53, 5.95, 5.52 ms, GRADIENT 4.02, 3.04, 2.80, 2.74; 250,047-particle FORCE
+// reverse FP32 260, 248, 228, 214 us; 27,000 ones FP64 FORCE 54, 43, 39, 31 us;
+// 8,000 ones FP32 63, 33, 17 and 14 us (the last two with 16 targets per
+// workgroup).  Culling and loading in one sweep instead of two was slower (441 us
+// for the column's 373): each source's fields then wait for its position.
+//
+// Where it is slower than one wavefront per 64 targets and records read from L1
+// (us, with that kernel's staging second): FP32 FORCE of a uniform gas of some
+// 200,000 particles and more, at 0.3 to 4 a bucket, so fewer than 20 neighbours
+// each (1 M particles at 0.3, 1 and 4 a bucket 222 and 157, 224 and 149, 256 and
+// 199; FP64 295 and 302, 302 and 304, 356 and 368): 64 targets then lie in 16 and
+// more buckets, share little of their window, and use few of its records.
 //
 // In the FP32-split form the position difference is rebuilt from bucket
 // indices and float offsets, d = (c_j - c_i) L + (off_j - off_i), which is
@@ -133,7 +141,7 @@ struct Pass {
     static constexpr int NV = NR / C + (REST > 0 && !HALF ? 1 : 0);
     // Wavefronts per SIMD: caps the registers at 512 / that and the LDS of a
     // workgroup at 160 KB / that (LDS is given out in 1,280 bytes).  The most
-    // at which little is spilled (ten registers at most, outside the loop over
+    // at which little is spilled (fifteen registers at most, outside the loop over
     // hits): one more is slower by 20 to 80 % (FP32 adjoint 278 -> 502 us), one
     // fewer by 2 to 30 %, as a page holds more but fewer wavefronts hide each
     // other's waits.  Small calls of the solid FORCE pass, whose workgroups are
@@ -1295,12 +1303,12 @@ hipError_t go(const Params &P, const Grid &g, const sph_particles &tg, const uin
     auto launch = [&](auto kernel, int group) { kernel<<<div_up(tg.n, group), kPairBlock, 0, s>>>(call); };
     // The fewest targets per wavefront whose workgroups are all resident at
     // once (one per SIMD's wavefront on each CU): below that a call is bound by
-    // the latency of one workgroup's chain of loads, barriers and bucket rows,
-    // which fewer targets shorten; above it their windows overlap more and the
-    // chip is full.  16, 8 and 4 targets, in us: FORCE FP32 of 1,728 particles
-    // 33, 19, 15; 8,000 28, 20, 17; 27,000 32, 28, 31; 46,656 37.5, 37.6, 45;
-    // 64,000 41, 47, 57; solid FP64 FORCE of 4,096 30, 22, 14; 13,824 33, 27,
-    // 30; its reverse (one workgroup per CU) 61, 38, 24 and 63, 65, 78.
+    // the latency of one workgroup's chain of loads and barriers, which fewer
+    // targets shorten; above it their windows overlap more and the chip is full.
+    // 16, 8 and 4 targets, in us a call (12 of them the launch): FORCE FP32 of
+    // 1,728 particles 20, 14, 12; 8,000 20, 14, 13; 27,000 22, 21, 27; 46,656 29,
+    // 31, 42; 64,000 33, 36, 52; solid FP64 FORCE of 4,096 25, 16, 14; 13,824 28,
+    // 21, 28; its reverse (one workgroup per CU) 35, 24, 20 and 41, 44, 64.
     using W4 = Pass<real, PASS, SOLID, 4>;
     using W8 = Pass<real, PASS, SOLID, 8>;
     if (div_up(tg.n, W4::kGroup) <= kCUs * W4::waves)
