@@ -516,7 +516,6 @@ void k_pairs(PairCall<real> call)
             T.o[d] = tg.off[d][i];
             T.x[d] = 0.0;
         } else {
-            tpos[d] = tg.x[d][ti];
             T.x[d] = tg.x[d][i];
             T.o[d] = real(0);
         }
@@ -645,6 +644,10 @@ void k_pairs(PairCall<real> call)
         const CallArgs<real> at_round = call_args<real>();
         const auto &g = at_round->g;
         T.Lf = SPLIT ? (real)g.Lf : real(0);
+        if constexpr (!SPLIT) {   // (read again in each round: six registers)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) tpos[d] = entry(at_round->tg.x[d], ti);
+        }
         // The next groups, of targets that share a bucket row: the first pending
         // target's and up to three more.  Lanes 16 k .. 16 k + 15 keep what
         // concerns group k: its row, the bucket its frame starts at, its buckets.
