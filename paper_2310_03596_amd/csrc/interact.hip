@@ -54,9 +54,9 @@
 // reads from L1 with their staging kernel first, whole windows in LDS second,
 // culled ones third, several rows together fourth: column FORCE FP32 401, 391,
 // 350, 330 us, FP64 675, 572, 520, 500; 4.0 M cylinder (FP32) FORCE 2.89, 2.59,
-// 2.23, 2.16 ms, GRADIENT 1.62, 1.50, 1.31, 1.31; 6.7 M impact (FP64) FORCE 8.83,
-// 6.53, 5.95, 5.52 ms, GRADIENT 4.02, 3.04, 2.80, 2.74; 250,047-particle FORCE
-// reverse FP32 260, 248, 228, 214 us; 27,000 ones FP64 FORCE 54, 43, 39, 31 us;
+// 2.23, 2.07 ms, GRADIENT 1.62, 1.50, 1.29, 1.27; 6.7 M impact (FP64) FORCE 8.83,
+// 6.53, 5.70, 5.58 ms, GRADIENT 4.02, 3.04, 2.71, 2.74; 250,047-particle FORCE
+// reverse FP32 260, 248, 228, 207 us; 27,000 ones FP64 FORCE 54, 43, 39, 31 us;
 // 8,000 ones FP32 63, 33, 17 and 14 us (the last two with 16 targets per
 // workgroup).  Culling and loading in one sweep instead of two was slower (441 us
 // for the column's 373): each source's fields then wait for its position.
@@ -141,7 +141,7 @@ struct Pass {
     static constexpr int NV = NR / C + (REST > 0 && !HALF ? 1 : 0);
     // Wavefronts per SIMD: caps the registers at 512 / that and the LDS of a
     // workgroup at 160 KB / that (LDS is given out in 1,280 bytes).  The most
-    // at which little is spilled (fifteen registers at most, outside the loop over
+    // at which little is spilled (ten registers at most, outside the loop over
     // hits): one more is slower by 20 to 80 % (FP32 adjoint 278 -> 502 us), one
     // fewer by 2 to 30 %, as a page holds more but fewer wavefronts hide each
     // other's waits.  Small calls of the solid FORCE pass, whose workgroups are
@@ -379,7 +379,7 @@ using CallArgs = const __attribute__((address_space(4))) PairCall<real> *;
 // The kernel's arguments, read again where they are used.  Some 40 pointers and
 // constants that stay in scalar registers from one use to the next push the loops'
 // own scalars out into vector registers (50 to 120 of them, and up to 23 vector
-// registers out into scratch, against 0 to 15 and up to 15: column FORCE FP32 356
+// registers out into scratch, against 0 to 16 and up to 10: column FORCE FP32 356
 // and 339 us, a share's sort and two passes 1,393 and 1,305).
 template <typename real>
 __device__ inline CallArgs<real> call_args()
@@ -507,12 +507,18 @@ void k_pairs(PairCall<real> call)
     PairK<real> K;
     real R2;
 
+    // The position of the lane's target for the culling is kept in the FP32 fluid FORCE
+    // pass and read again in each round in the others, which are short of its three
+    // registers (FP64: six): 4 M cylinder GRADIENT FP32 1,310 us kept and 1,268 read
+    // again, 6.7 M impact FORCE FP32 3,490 and 3,420, FP64 5,690 and 5,580,
+    // 250,047-particle FORCE reverse FP32 215 and 207, but column step FP32 382 and 384.
+    constexpr bool KEPT = SPLIT && FORCE && !SOLID;
+    real tpos[3];
     TargetPos<real> T;
-    real tpos[3];   // of the lane's target
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
+        if constexpr (KEPT) tpos[d] = tg.off[d][ti];
         if constexpr (SPLIT) {
-            tpos[d] = tg.off[d][ti];
             T.o[d] = tg.off[d][i];
             T.x[d] = 0.0;
         } else {
@@ -644,9 +650,14 @@ void k_pairs(PairCall<real> call)
         const CallArgs<real> at_round = call_args<real>();
         const auto &g = at_round->g;
         T.Lf = SPLIT ? (real)g.Lf : real(0);
-        if constexpr (!SPLIT) {   // (read again in each round: six registers)
+        if constexpr (!KEPT) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d) tpos[d] = entry(at_round->tg.x[d], ti);
+            for (int d = 0; d < 3; ++d) {
+                if constexpr (SPLIT)
+                    tpos[d] = entry(at_round->tg.off[d], ti);
+                else
+                    tpos[d] = entry(at_round->tg.x[d], ti);
+            }
         }
         // The next groups, of targets that share a bucket row: the first pending
         // target's and up to three more.  Lanes 16 k .. 16 k + 15 keep what
